@@ -20,6 +20,19 @@ namespace {
 
 constexpr int kMaxBins = 4096;
 
+// The bin of a smoothed pixel.
+__device__ __forceinline__ int log_bin(double acc, double mu_ref, int nbins, double lo, double hi) {
+#pragma clang fp contract(off)
+    int b = 0;
+    if (acc > 0.0) {
+        const double v = log10(acc / mu_ref);
+        const double u = ((v - lo) / (hi - lo)) * (double)nbins;
+        if (u >= (double)nbins) b = nbins - 1;
+        else if (u > 0.0) b = (int)floor(u);
+    }
+    return b;
+}
+
 // Column pass for pixel (i, j) of the valid interior, then its bin, counted
 // in an LDS histogram and added to the global bin counts.
 __global__ __launch_bounds__(kSmoothThreads) void smooth_cols_hist_kernel(
@@ -35,18 +48,62 @@ __global__ __launch_bounds__(kSmoothThreads) void smooth_cols_hist_kernel(
         const double *col = tmp + (int64_t)j * wx + i;
         double acc = 0.0;
         for (int k = 0; k <= 2 * ry; ++k) acc = acc + gy[k] * col[(int64_t)k * wx];
-        int b = 0;
-        if (acc > 0.0) {
-            const double v = log10(acc / mu_ref);
-            const double u = ((v - lo) / (hi - lo)) * (double)nbins;
-            if (u >= (double)nbins) b = nbins - 1;
-            else if (u > 0.0) b = (int)floor(u);
-        }
-        atomicAdd(&h[b], 1u);
+        atomicAdd(&h[log_bin(acc, mu_ref, nbins, lo, hi)], 1u);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < nbins; b += kSmoothThreads)
         if (h[b]) atomicAdd(&bins[b], h[b]);
+}
+
+// Column pass of radii up to kTapsMaxRadius with the binning; the workgroup
+// that finishes last normalises the counts into hist (if wanted).  R pixels a
+// thread also means that many fewer workgroups that add to the same few bins.
+template <int R>
+__global__ __launch_bounds__(kSmoothThreads) void slide_cols_hist_kernel(
+    const double *__restrict__ tmp, int wx, int wy, double sigma, double pixel, int ry, double mu_ref, int nbins,
+    double lo, double hi, unsigned *__restrict__ bins, float *__restrict__ hist, unsigned *__restrict__ done) {
+    __shared__ double taps[kTapsLds], total;
+    extern __shared__ unsigned h[];   // nbins
+    __shared__ unsigned long long sum;
+    __shared__ bool last;
+    for (int b = threadIdx.x; b < nbins; b += kSmoothThreads) h[b] = 0;
+    taps_to_lds(sigma, pixel, ry, taps, &total);
+    const int idx = blockIdx.x * kSmoothThreads + threadIdx.x;
+    const int j0 = (idx / wx) * R, i = idx % wx;
+    if (j0 < wy) {
+        double acc[R];
+        slide_columns<R>(tmp, wx, i, j0, wy + 2 * ry - 1, taps, ry, acc);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (j0 + r < wy) atomicAdd(&h[log_bin(acc[r], mu_ref, nbins, lo, hi)], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < nbins; b += kSmoothThreads)
+        if (h[b]) atomicAdd(&bins[b], h[b]);
+    if (!hist) return;   // uniform
+    // The bins are only ever touched by atomics, which are done where every
+    // compute unit sees them, so the tick has to wait for this workgroup's
+    // atomics and no more: a fence for the device would write back the L2
+    // (30 us here).
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   // (for the compiler)
+    __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0): the wave's atomics are done
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        last = atomicAdd(done, 1u) == gridDim.x - 1;
+        sum = 0;
+    }
+    __syncthreads();
+    if (!last) return;
+    unsigned long long t = 0;
+    for (int b = threadIdx.x; b < nbins; b += kSmoothThreads) {
+        h[b] = atomicAdd(&bins[b], 0u);
+        t += h[b];
+    }
+    if (t) atomicAdd(&sum, t);
+    __syncthreads();
+    for (int b = threadIdx.x; b < nbins; b += kSmoothThreads)
+        hist[b] = sum ? (float)((double)h[b] / (double)sum) : 0.0f;
 }
 
 __global__ void zero_bins_kernel(unsigned *bins, int n) {
@@ -116,6 +173,22 @@ extern "C" int raysh_log_mag_histogram(const int32_t *counts, int32_t nx, int32_
 
     hipStream_t s = (hipStream_t)hip_stream;
     double *tmp = (double *)workspace;                      // ny * wx
+    if (rx <= kTapsMaxRadius && ry <= kTapsMaxRadius) {
+        unsigned *done = (unsigned *)(tmp + (size_t)ny * wx);   // workgroups of the column pass that have finished
+        launch_smooth_rows(s, counts, nx, ny, norm, sigma, px, rx, wx, tmp, (unsigned *)bin_counts, nbins, done);
+        const int R = slide_rows_per_thread((int64_t)wx * wy);
+        const dim3 grid(slide_blocks(wx, wy, R));
+        const size_t lds = (size_t)nbins * sizeof(unsigned);
+#define RAYSH_CASE(N)                                                                                              \
+    if (R == N)                                                                                                    \
+        hipLaunchKernelGGL(slide_cols_hist_kernel<N>, grid, dim3(kSmoothThreads), lds, s, tmp, wx, wy, sigma, py,   \
+                           ry, mu_ref, nbins, lo, hi, (unsigned *)bin_counts, hist, done);
+        RAYSH_CASE(4) RAYSH_CASE(8)
+#undef RAYSH_CASE
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return hip_error(e, "raysh_log_mag_histogram");
+        return set_ok();
+    }
     double *gxt = tmp + (size_t)ny * wx;                    // 2 rx + 1
     double *gyt = gxt + (2 * rx + 1);                       // 2 ry + 1
     hipLaunchKernelGGL(taps_kernel, dim3(1), dim3(kSmoothThreads), 0, s, sigma, px, rx, gxt);
