@@ -71,7 +71,7 @@ enum {
                                 radius) enter through one local Taylor expansion
                                 of their summed term (order
                                 raysh_expansion_order()), the others directly.
-                                Regions are blocks of 64 x 64 ray tiles, whose
+                                Regions are blocks of tiles of 4096 rays, whose
                                 expansion is re-centred on each tile, and the
                                 tiles themselves, which re-test only the block's
                                 near stars (raysh_set_expansion_block).
@@ -175,7 +175,7 @@ int raysh_set_tile(raysh_ctx *ctx, int precision, int cx, int cy, int share, int
 int raysh_set_expansion(raysh_ctx *ctx, double theta_open);
 
 /* Workgroup shape of RAYSH_FP64_EXPANSION for this context: each workgroup
- * expands the stars far from a block of block x block tiles of 64 x 64 rays
+ * expands the stars far from a block of block x block tiles of 4096 rays
  * once, then re-tests only that block's near stars for each tile (block 1:
  * one tile, one test).  0 (the default) picks the block by a cost model:
  * a workgroup costs about n_stars + 16384 block^2 star-equivalents, and

@@ -51,6 +51,34 @@ __device__ __forceinline__ int32_t source_pixel(const ShootParams &p, double tx,
     return js * p.NX + is;
 }
 
+// (beta - origin) / P rounded to nearest, as the division would round it, for
+// y = RN(1 / P): q is corrected twice by its residual, which leaves it within
+// one unit in the last place after the first step and equal to the rounded
+// quotient after the second (Markstein's theorem: with y the rounded
+// reciprocal and q a faithful quotient, RN(q + y RN(d - q P)) = RN(d / P)).
+// Five instructions where the division takes thirteen, several of them at a
+// quarter of the rate.  The residuals are exact unless something under- or
+// overflows: the host allows this form only for pixel sizes and origins that
+// rule out underflow (fast_pixels), and a quotient beyond the range of FP64
+// comes out as NaN or infinity, which no window holds.
+__device__ __forceinline__ double pixel_coordinate(double beta, double origin, double P, double y) {
+#pragma clang fp contract(off)
+    const double d = beta - origin;
+    double q = d * y;
+    q = __builtin_fma(__builtin_fma(-q, P, d), y, q);
+    return __builtin_fma(__builtin_fma(-q, P, d), y, q);
+}
+
+// The pixel step of Algorithm 1: the pixel coordinates (beta - X0) / P as
+// IEEE division rounds them, the half-open window test in FP64, and floor.
+// is, js: the pixel, or -1 when beta is outside the window or not finite (a
+// NaN or an infinity fails the test as it stands).
+__device__ __forceinline__ void window_pixel(const ShootParams &p, double u, double v, int32_t &is, int32_t &js) {
+    const bool in = u >= 0.0 && u < (double)p.NX && v >= 0.0 && v < (double)p.NY;
+    is = in ? (int32_t)u : -1;   // u >= 0: truncation is floor
+    js = in ? (int32_t)v : -1;
+}
+
 __device__ __forceinline__ long long wave_sum(long long v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -155,6 +183,53 @@ __device__ __forceinline__ void finish_tile(const ShootParams &p, BinShared &sh,
         }
     }
     if (threadIdx.x == 0 && p.n_binned) atomicAdd(p.n_binned, (unsigned long long)total);
+}
+
+// 1 / r[i] for N values from one hardware reciprocal (good to about 2^-24)
+// of their product, refined by one Newton step (to about 2^-48).  The
+// product is built as a balanced tree (N - 1 multiplies); walking the tree
+// back down, each node's inverse times its sibling's product is the inverse
+// of the node's other child (2 multiplies per node), so the leaves receive
+// 1 / r[i].  Cost: 3 (N - 1) multiplies, one reciprocal, two FMAs.
+template <int N>
+__device__ __forceinline__ double tree_product(const double *r) {
+    if constexpr (N == 1) return r[0];
+    else return tree_product<N / 2>(r) * tree_product<N / 2>(r + N / 2);
+}
+
+template <int N>
+__device__ __forceinline__ void tree_inverse(const double *r, double y, double *inv) {
+    if constexpr (N == 1) {
+        inv[0] = y;
+    } else {
+        const double lo = tree_product<N / 2>(r);       // common subexpressions of the up-sweep
+        const double hi = tree_product<N / 2>(r + N / 2);
+        tree_inverse<N / 2>(r, hi * y, inv);           // 1 / (product of the lower half)
+        tree_inverse<N / 2>(r + N / 2, lo * y, inv + N / 2);
+    }
+}
+
+template <int N>
+__device__ __forceinline__ void reciprocals(const double *r, double *inv) {
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8 || N == 16, "N is a power of two");
+    const double pr = tree_product<N>(r);
+    double y = __builtin_amdgcn_rcp(pr);
+    const double e = __builtin_fma(-pr, y, 1.0);
+    y = __builtin_fma(y, e, y);
+    tree_inverse<N>(r, y, inv);
+}
+
+// m / r[i] for N values that share the numerator m: the root's inverse is
+// scaled by m inside its Newton step (t = m y, then t + t e with
+// e = 1 - p y), so the leaves receive m / r[i] for one multiply per group.
+template <int N>
+__device__ __forceinline__ void scaled_reciprocals(const double *r, double m, double *inv) {
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8 || N == 16, "N is a power of two");
+    const double pr = tree_product<N>(r);
+    const double y = __builtin_amdgcn_rcp(pr);
+    const double e = __builtin_fma(-pr, y, 1.0);
+    const double t = m * y;
+    tree_inverse<N>(r, __builtin_fma(t, e, t), inv);
 }
 
 // Star records read through the constant address space: no kernel writes

@@ -113,9 +113,9 @@ int launch(raysh_ctx *c, const ShootParams &p, int precision, const char *what) 
             }
             cells = c->cells.view;
         }
-        const int block =
-            c->expansion_block ? c->expansion_block : raysh::expansion_block(p.nx, p.ny, c->n_stars, c->n_cu);
-        const size_t need = raysh::expansion_workspace_bytes(p.nx, p.ny, block);
+        const raysh::TileGrid tiles = raysh::expansion_tiles(p.nx, p.ny, p.dx, p.dy);
+        const int block = c->expansion_block ? c->expansion_block : raysh::expansion_block(tiles, c->n_stars, c->n_cu);
+        const size_t need = raysh::expansion_workspace_bytes(tiles, block);
         if (need > c->far_bytes) {
             e = hipStreamSynchronize(c->stream);   // the old workspace may still be read
             if (e != hipSuccess) return hip_error(e, what);
@@ -130,7 +130,7 @@ int launch(raysh_ctx *c, const ShootParams &p, int precision, const char *what) 
             }
             c->far_bytes = need;
         }
-        e = raysh::launch_shoot_expansion(p, cells, c->theta_open, block, c->d_far, c->stream);
+        e = raysh::launch_shoot_expansion(p, cells, c->theta_open, tiles, block, c->d_far, c->stream);
     }
     if (e != hipSuccess) return hip_error(e, what);
     return RAYSH_OK;
@@ -323,6 +323,17 @@ void fill_shoot_params(ShootParams &p, const raysh_ctx *c, const raysh_rays *r,
     p.Py = w->py;
     p.NX = w->nx;
     p.NY = w->ny;
+    p.ipx = 1.0 / w->px;
+    p.ipy = 1.0 / w->py;
+    // pixel_coordinate's quotients equal IEEE division when nothing
+    // underflows.  With |X0| >= 2^-400 a nonzero beta - X0 is at least
+    // 2^-454 (the two are within a factor of two and differ by a unit in
+    // X0's last place, or they differ by half of X0), so for P in
+    // [2^-300, 2^300] the quotient (above 2^-755) and its residuals (2^-53 to
+    // 2^-107 of the difference) stay normal numbers.  Other windows divide.
+    const auto size_ok = [](double P) { return P >= 0x1p-300 && P <= 0x1p300; };
+    const auto origin_ok = [](double x) { return std::fabs(x) >= 0x1p-400 && std::fabs(x) <= 0x1p300; };
+    p.fast_pixels = size_ok(w->px) && size_ok(w->py) && origin_ok(w->x0) && origin_ok(w->y0);
 }
 
 extern "C" {

@@ -28,7 +28,9 @@ struct ShootParams {
     int64_t nx, ny, i0, j0;
     // source window
     double X0, Y0, Px, Py;
+    double ipx, ipy;           // 1 / Px, 1 / Py
     int32_t NX, NY;
+    int32_t fast_pixels;       // the pixel step may use them (pixel_coordinate)
     // outputs (any may be null)
     double *beta_x, *beta_y;
     int32_t *bin;
@@ -113,18 +115,25 @@ struct StarCellStore {
 hipError_t build_star_cells(const Star *d_stars, int64_t n_stars, hipStream_t s, StarCellStore &out);
 void free_star_cells(StarCellStore &cells);
 
-// FP64 with the far field as local expansions (shoot_expansion.hip); tiles
-// of 64 x 64 rays in blocks of `block` x `block` tiles (1, 2 or 4): one
-// workgroup per block for the pass over the stars, one per row of a block's
-// tiles for the tiles.  expansion_block picks the block for a lattice block.  With
-// cells (cells.ncx > 0) the block pass takes distant cells through their
-// multipole expansions.
-hipError_t launch_shoot_expansion(const ShootParams &p, const StarCells &cells, double theta_open, int block,
-                                  void *workspace, hipStream_t s);
-// Device workspace launch_shoot_expansion needs for an nx x ny lattice block
-// (each workgroup block's coefficients and near-star lists, about 8.6 KB each).
-size_t expansion_workspace_bytes(int64_t nx, int64_t ny, int block);
-int expansion_block(int64_t nx, int64_t ny, int64_t n_stars, int n_cu);
+// Ray tiles of a lattice block in the expansion mode (shoot_expansion.hip):
+// tiles of w x h = 64 / 2^skew x 64 * 2^skew rays.
+struct TileGrid {
+    int skew, w, h;
+    int64_t tiles_x, tiles_y;
+};
+TileGrid expansion_tiles(int64_t nx, int64_t ny, double dx, double dy);
+
+// FP64 with the far field as local expansions (shoot_expansion.hip); tiles in
+// blocks of `block` x `block` (1, 2 or 4): one workgroup per block for the
+// pass over the stars, then one for a tile or a few.  expansion_block picks
+// the block for a lattice block.  With cells (cells.ncx > 0) the block pass
+// takes distant cells through their multipole expansions.
+hipError_t launch_shoot_expansion(const ShootParams &p, const StarCells &cells, double theta_open, const TileGrid &g,
+                                  int block, void *workspace, hipStream_t s);
+// Device workspace launch_shoot_expansion needs (each block's coefficients and
+// near-star lists, about 8.6 KB each).
+size_t expansion_workspace_bytes(const TileGrid &g, int block);
+int expansion_block(const TileGrid &g, int64_t n_stars, int n_cu);
 int expansion_order();
 
 hipError_t launch_zero_u64(unsigned long long *p, int n, hipStream_t s);

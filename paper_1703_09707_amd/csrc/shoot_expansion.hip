@@ -19,23 +19,21 @@
 // whose truncation error stays at the level of FP64 rounding.
 //
 // Two levels.  The lattice is cut into blocks of L x L ray tiles (a tile is
-// 64 x 64 rays, 4 x 4 per lane as in the one-pass kernel).  One workgroup
-// per block expands the stars far from the whole block once (every star is
-// visited once per block, not once per tile), keeping the block's near
-// stars in lists.  Then one workgroup per row of the block's tiles
-// re-centres the block's polynomial on each of its tiles (the shift of a
-// polynomial is exact algebra: no new truncation), and for each tile
-//   * re-tests only the block's near stars: those far from the tile join
-//     its polynomial, the rest are summed directly,
-//   * evaluates the polynomial for its rays (Horner), adds the near stars
-//     and bins the rays.
+// 4096 rays, 64 x 64 or a rectangle).  One workgroup per block expands the
+// stars far from the whole block once (every star is visited once per block,
+// not once per tile), keeping the block's near stars in lists.  Then a second
+// kernel re-centres the block's polynomial on each tile (the shift of a
+// polynomial is exact algebra: no new truncation), re-tests only the block's
+// near stars (those far from the tile join its polynomial, the rest are
+// summed directly), re-centres the tile's polynomial on 16 patches of 256
+// rays, and evaluates those (Horner), adds the near stars and bins the rays.
 // With L = 1 the block is the tile and the second test is skipped.  If a
 // block has more near stars than its lists hold, its tiles sum every star
 // directly.
 //
 // The block pass is a kernel of its own (expansion_block_kernel), which
 // leaves each block's polynomial and near lists in a workspace for the
-// tile kernel (expansion_fp64_kernel); each runs at the occupancy its own
+// tile kernel (expansion_tile_kernel); each runs at the occupancy its own
 // registers allow.
 //
 // Star cells.  Optionally the stars are sorted once by the cell of a
@@ -58,11 +56,16 @@ namespace {
 constexpr int kOrder = 24;            // Taylor terms B_0 .. B_kOrder
 constexpr int kWaves = kThreads / 64;
 constexpr int kNearPerWave = 512;     // near-star list capacity of each wave
-constexpr int kCX = 4, kCY = 4;       // rays per lane
-constexpr int kTile = kLanesX * kCX;  // 64 rays per tile side
-static_assert(kLanesX * kCX == kLanesY * kCY, "square tiles");
-
-constexpr int kMaxTiles = 16;         // tiles per workgroup block, at most 4 x 4
+// A tile is 4096 rays, 64 x 64 for a lattice of square cells.  For others it
+// is 64 / 2^k by 64 * 2^k (expansion_tiles), so that its sides come out as equal as
+// they can: near lists, and with them the stars summed directly, grow as the
+// square of its radius.  A patch is a quarter of the tile either way.
+constexpr int kPatchRays = 256;       // 16 x 16 / 2^k by 16 * 2^k
+constexpr int kPatchSide = 4;         // patches along a tile's sides
+constexpr int kPatches = kPatchSide * kPatchSide;
+constexpr int kMaxSkew = 2;           // |k|
+constexpr int kPatchOrder = 13;       // Taylor terms of a patch's polynomial (see expansion_tile_kernel)
+constexpr int kTileNear = 256;        // near-star list capacity of a tile
 constexpr int kCellMaxRows = kThreads;   // star-cell grid rows and columns: one thread per row
 constexpr int kCellMaxCells = 4096;
 constexpr int64_t kCellMaxStars = int64_t(1) << 26;   // the host keeps two copies while building
@@ -70,12 +73,9 @@ constexpr int32_t kCellMaxPerCell = 1 << 20;          // stars of one cell (its 
 
 struct ExpShared {
     double2 A[kOrder + 1];                      // the block's coefficients
-    double2 B[kMaxTiles][kOrder + 1];           // each tile's coefficients (blocks of more than one tile)
     double2 part[kWaves][kOrder + 1];           // per-wave partial sums
     int outer_idx[kWaves][kNearPerWave];        // the block's near stars, each wave's in index order
     int outer_n[kWaves];
-    int inner_idx[kWaves][kNearPerWave];        // the tile's near stars (a subset of the block's)
-    int inner_n[kWaves];
     int row_lo[kCellMaxRows], row_hi[kCellMaxRows];   // each star-cell row's band of open cells
     int row_first[kCellMaxRows];                      // first record of the band's stars
     int row_pref[kCellMaxRows];                       // the bands' stars before this row
@@ -95,25 +95,25 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
     return make_double2(__builtin_fma(a.x, b.x, -a.y * b.y), __builtin_fma(a.x, b.y, a.y * b.x));
 }
 
-// Centre and radius (centre to corner ray, slightly enlarged) of the square
-// of w x w lattice points whose first point is (i, j) of the block.
-__device__ __forceinline__ void region(const ShootParams &p, int64_t i, int64_t j, int w, double &cx,
+// Centre and radius (centre to corner ray, slightly enlarged) of the rectangle
+// of w x h lattice points whose first point is (i, j) of the block.
+__device__ __forceinline__ void region(const ShootParams &p, int64_t i, int64_t j, int w, int h, double &cx,
                                        double &cy, double &rho) {
     const double x_first = image_angle(p.x0, p.i0 + i, p.dx);
     const double x_last = image_angle(p.x0, p.i0 + i + w - 1, p.dx);
     const double y_first = image_angle(p.y0, p.j0 + j, p.dy);
-    const double y_last = image_angle(p.y0, p.j0 + j + w - 1, p.dy);
+    const double y_last = image_angle(p.y0, p.j0 + j + h - 1, p.dy);
     cx = 0.5 * (x_first + x_last);
     cy = 0.5 * (y_first + y_last);
     const double hx = 0.5 * (x_last - x_first), hy = 0.5 * (y_last - y_first);
     rho = __builtin_sqrt(hx * hx + hy * hy) * (1.0 + 1e-12) + 1e-290;
 }
 
-// region() for a square every lane of the wave shares: the results are
+// region() for a rectangle every lane of the wave shares: the results are
 // moved to scalar registers.
-__device__ __forceinline__ void region_uniform(const ShootParams &p, int64_t i, int64_t j, int w, double &cx,
+__device__ __forceinline__ void region_uniform(const ShootParams &p, int64_t i, int64_t j, int w, int h, double &cx,
                                                double &cy, double &rho) {
-    region(p, i, j, w, cx, cy, rho);
+    region(p, i, j, w, h, cx, cy, rho);
     cx = uniform_f64(cx);
     cy = uniform_f64(cy);
     rho = uniform_f64(rho);
@@ -231,19 +231,35 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int *wave_tot, int *t
     return before + incl - v;
 }
 
-// Workgroup sum of the lanes' coefficients into dst (added to it when ADD),
-// in a fixed order.  Within a wave the 2 (kOrder + 1) real components,
-// padded with zeros to 64 slots, are reduced by recursive halving: at the
-// step of lane mask m, lanes with that bit keep the upper half of their
-// slots and the others the lower half, each adds the half its partner
-// sends, so after six steps lane l holds the wave's sum of slot l (126
-// exchanges per lane instead of 300 for a butterfly over every slot).
-// The waves' sums are then added in turn.
-template <bool ADD>
-__device__ __forceinline__ void reduce_coeffs(double2 (&acc)[kOrder + 1], ExpShared &ex, double2 *dst) {
+// The sum a lane keeps when lanes with bit W set take `upper` and the others
+// `lower`, its own plus the one of its partner across that bit.
+template <int W>
+__device__ __forceinline__ double swap_halves(double lower, double upper) {
+    const uint64_t a = __builtin_bit_cast(uint64_t, lower), b = __builtin_bit_cast(uint64_t, upper);
+    typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+    uint2v lo, hi;
+    if constexpr (W == 32) {
+        lo = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+        hi = __builtin_amdgcn_permlane32_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+    } else {
+        lo = __builtin_amdgcn_permlane16_swap((unsigned)a, (unsigned)b, false, false);
+        hi = __builtin_amdgcn_permlane16_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+    }
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+
+// Wave sum of the lanes' coefficients in a fixed order: lane l < 2 (kOrder + 1)
+// returns real component l.  The components, padded with zeros to 64 slots,
+// are reduced by recursive halving: at the step of lane mask m, lanes with
+// that bit keep the upper half of their slots and the others the lower half,
+// each adds the half its partner sends, so after six steps lane l holds the
+// wave's sum of slot l (63 exchanges per lane instead of 300 for a butterfly
+// over every slot).
+__device__ __forceinline__ double wave_reduce_coeffs(const double2 (&acc)[kOrder + 1]) {
     constexpr int kSlots = 2 * (kOrder + 1);
     static_assert(kSlots <= 64, "one slot per lane at the end");
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const int lane = threadIdx.x % 64;
     double v[64];
 #pragma unroll
     for (int q = 0; q <= kOrder; ++q) {
@@ -252,8 +268,14 @@ __device__ __forceinline__ void reduce_coeffs(double2 (&acc)[kOrder + 1], ExpSha
     }
 #pragma unroll
     for (int i = kSlots; i < 64; ++i) v[i] = 0.0;
+    // lane bits 5 and 4: v_permlane*_swap exchanges the halves (rows) of two
+    // registers, after which both hold what one lane is to add
 #pragma unroll
-    for (int n = 64; n > 1; n /= 2) {
+    for (int i = 0; i < 32; ++i) v[i] = swap_halves<32>(v[i], v[i + 32]);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = swap_halves<16>(v[i], v[i + 16]);
+#pragma unroll
+    for (int n = 16; n > 1; n /= 2) {
         const int m = n / 2;                 // the lane bit of this step
         const bool upper = (lane & m) != 0;
 #pragma unroll
@@ -263,73 +285,23 @@ __device__ __forceinline__ void reduce_coeffs(double2 (&acc)[kOrder + 1], ExpSha
             v[i] = keep + __shfl_xor(send, m, 64);
         }
     }
-    double *part = reinterpret_cast<double *>(&ex.part[wave][0]);
-    if (lane < kSlots) part[lane] = v[0];
+    return v[0];
+}
+
+// Workgroup sum of the lanes' coefficients into dst: the waves' sums, added
+// in turn.
+__device__ __forceinline__ void reduce_coeffs(double2 (&acc)[kOrder + 1], ExpShared &ex, double2 *dst) {
+    constexpr int kSlots = 2 * (kOrder + 1);
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const double v = wave_reduce_coeffs(acc);
+    if (lane < kSlots) reinterpret_cast<double *>(&ex.part[wave][0])[lane] = v;
     __syncthreads();
     if (threadIdx.x < kSlots) {
         double t = reinterpret_cast<const double *>(&ex.part[0][0])[threadIdx.x];
         for (int w = 1; w < kWaves; ++w) t += reinterpret_cast<const double *>(&ex.part[w][0])[threadIdx.x];
-        double *d = reinterpret_cast<double *>(dst);
-        if (ADD) t += d[threadIdx.x];
-        d[threadIdx.x] = t;
+        reinterpret_cast<double *>(dst)[threadIdx.x] = t;
     }
     __syncthreads();
-}
-
-// Binomial coefficients C(n, k) for n, k <= kOrder: exact integers (at most
-// C(24, 12)) built by Pascal's rule at compile time.
-struct BinomialTable {
-    double c[kOrder + 1][kOrder + 1];
-};
-
-constexpr BinomialTable make_binomials() {
-    BinomialTable t{};
-    for (int n = 0; n <= kOrder; ++n) {
-        t.c[n][0] = 1.0;
-        for (int k = 1; k <= n; ++k) t.c[n][k] = t.c[n - 1][k - 1] + (k < n ? t.c[n - 1][k] : 0.0);
-    }
-    return t;
-}
-
-__constant__ BinomialTable kBinomial = make_binomials();
-
-// Coefficient r of the block's polynomial re-centred on a tile: with
-// s = a + b s' (a = (c - C) / R, b = rho / R),
-//   B_r = b^r sum_{q=r}^{kOrder} A_q C(q, r) a^(q - r),
-// summed by Horner in a from q = kOrder down.
-__device__ __forceinline__ double2 shift_coeff(const double2 *A, int r, double2 a, double b) {
-    double2 acc = make_double2(A[kOrder].x * kBinomial.c[kOrder][r], A[kOrder].y * kBinomial.c[kOrder][r]);
-    for (int q = kOrder - 1; q >= r; --q) {
-        const double c = kBinomial.c[q][r];
-        const double2 t = cmul(acc, a);
-        acc = make_double2(t.x + A[q].x * c, t.y + A[q].y * c);
-    }
-    double br = 1.0;
-    for (int i = 0; i < r; ++i) br *= b;
-    return make_double2(acc.x * br, acc.y * br);
-}
-
-// The FP64 term of star k for a lane's rays (reciprocal plus one Newton
-// step, as in the one-pass kernel).
-__device__ __forceinline__ void direct_star(const ConstStar *st, int k, const double (&tx)[kCX],
-                                            const double (&ty)[kCY], double (&ax)[kCY][kCX],
-                                            double (&ay)[kCY][kCX]) {
-    const double sx = st[k].x, sy = st[k].y, sm = st[k].m;
-#pragma unroll
-    for (int b = 0; b < kCY; ++b) {
-        const double ey = ty[b] - sy;
-#pragma unroll
-        for (int a = 0; a < kCX; ++a) {
-            const double ex_ = tx[a] - sx;
-            const double r2 = __builtin_fma(ex_, ex_, ey * ey);
-            double y = __builtin_amdgcn_rcp(r2);
-            const double e = __builtin_fma(-r2, y, 1.0);
-            y = __builtin_fma(y, e, y);
-            const double wgt = sm * y;
-            ax[b][a] = __builtin_fma(wgt, ex_, ax[b][a]);
-            ay[b][a] = __builtin_fma(wgt, ey, ay[b][a]);
-        }
-    }
 }
 
 // The block pass over star cells.  A cell whose centre is at least
@@ -403,7 +375,7 @@ __device__ __forceinline__ void block_pass_cells(const StarCells &cells, double 
         bcx, bcy, brho, r_near2, acc, ex.outer_idx, ex.outer_n);
 }
 
-// The block pass, one workgroup per block of block_rays x block_rays rays:
+// The block pass, one workgroup per block of block_w x block_h rays:
 // the stars far from the block enter its local expansion A (through star
 // cells when CELLS), the near ones go to its lists; both are written to
 // far[blockIdx.x] for the tile kernel.  Two workgroups per compute unit: the
@@ -411,15 +383,16 @@ __device__ __forceinline__ void block_pass_cells(const StarCells &cells, double 
 template <bool CELLS>
 __global__ __launch_bounds__(kThreads, 2) void expansion_block_kernel(ShootParams p, StarCells cells,
                                                                       double theta_open, int blocks_x,
-                                                                      int block_rays, BlockFar *__restrict__ far) {
+                                                                      int block_w, int block_h,
+                                                                      BlockFar *__restrict__ far) {
     __shared__ ExpShared ex;
-    const int64_t b_i = (int64_t)(blockIdx.x % blocks_x) * block_rays;
-    const int64_t b_j = (int64_t)(blockIdx.x / blocks_x) * block_rays;
+    const int64_t b_i = (int64_t)(blockIdx.x % blocks_x) * block_w;
+    const int64_t b_j = (int64_t)(blockIdx.x / blocks_x) * block_h;
     const ConstStar *st = const_stars(uniform_ptr(p.stars));
     const int n = uniform(p.n_stars);
     const double inv_theta = uniform_f64(1.0 / theta_open);
     double bcx, bcy, brho;
-    region_uniform(p, b_i, b_j, block_rays, bcx, bcy, brho);
+    region_uniform(p, b_i, b_j, block_w, block_h, bcx, bcy, brho);
     double2 acc[kOrder + 1];
 #pragma unroll
     for (int q = 0; q <= kOrder; ++q) acc[q] = make_double2(0.0, 0.0);
@@ -438,7 +411,7 @@ __global__ __launch_bounds__(kThreads, 2) void expansion_block_kernel(ShootParam
             },
             bcx, bcy, brho, r_near2, acc, ex.outer_idx, ex.outer_n);
     }
-    reduce_coeffs<false>(acc, ex, ex.A);   // its barriers also publish outer_n
+    reduce_coeffs(acc, ex, ex.A);   // its barriers also publish outer_n
     BlockFar *f = far + blockIdx.x;
     if (threadIdx.x <= kOrder) f->A[threadIdx.x] = ex.A[threadIdx.x];
     if (threadIdx.x < kWaves) f->outer_n[threadIdx.x] = ex.outer_n[threadIdx.x];
@@ -448,184 +421,592 @@ __global__ __launch_bounds__(kThreads, 2) void expansion_block_kernel(ShootParam
     }
 }
 
-// The tiles of a block of L x L tiles, after its block pass: workgroup g
-// takes tiles [TPW s, TPW (s + 1)) of block g / (L^2 / TPW), s = g mod
-// (L^2 / TPW).  WPS waves per SIMD (workgroups per compute unit).
-template <int L, int TPW, int WPS>
-__global__ __launch_bounds__(kThreads, WPS) void expansion_fp64_kernel(ShootParams p, double theta_open,
-                                                                       int blocks_x,
-                                                                       const BlockFar *__restrict__ far) {
-    static_assert(TPW >= 1 && (L * L) % TPW == 0, "whole groups of a block's tiles");
-    constexpr int kSubs = L * L / TPW;
-    __shared__ BinShared sh;
-    __shared__ ExpShared ex;
-    bin_shared_init(sh);
-    for (int t = threadIdx.x; t < kWinX * kWinY; t += kThreads) sh.win[t] = 0;   // kept clear by finish_tile
+// q!, q <= kOrder (rounded from 23! on).
+struct FactorialTable {
+    double f[kOrder + 1];
+};
 
-    const int lx = threadIdx.x % kLanesX;
-    const int ly = threadIdx.x / kLanesX;
-    const int blk = (int)(blockIdx.x / kSubs);
-    const int t_begin = (int)(blockIdx.x % kSubs) * TPW, t_end = t_begin + TPW;
-    const int64_t b_i = (int64_t)(blk % blocks_x) * (kTile * L);
-    const int64_t b_j = (int64_t)(blk / blocks_x) * (kTile * L);
-    const ConstStar *st = const_stars(uniform_ptr(p.stars));
-    const int n = uniform(p.n_stars);
-    const double inv_theta = uniform_f64(1.0 / theta_open);
+constexpr FactorialTable make_factorials() {
+    FactorialTable t{};
+    t.f[0] = 1.0;
+    for (int q = 1; q <= kOrder; ++q) t.f[q] = t.f[q - 1] * q;
+    return t;
+}
 
-    // --- the block: its coefficients A and near stars, from the block pass
-    double bcx, bcy, brho;
-    region_uniform(p, b_i, b_j, kTile * L, bcx, bcy, brho);
-    {
-        const BlockFar *f = far + blk;
-        if (threadIdx.x <= kOrder) ex.A[threadIdx.x] = f->A[threadIdx.x];
-        if (threadIdx.x < kWaves) ex.outer_n[threadIdx.x] = f->outer_n[threadIdx.x];
-        for (int w = 0; w < kWaves; ++w) {
-            const int cnt = min(uniform(f->outer_n[w]), kNearPerWave);
-            for (int i = threadIdx.x; i < cnt; i += kThreads) ex.outer_idx[w][i] = f->outer_idx[w][i];
-        }
-        __syncthreads();
-    }
-    bool overflow = false;
-    int n_outer = 0;
-    for (int w = 0; w < kWaves; ++w) {
-        overflow |= ex.outer_n[w] > kNearPerWave;
-        n_outer += ex.outer_n[w];
-    }
-    if (L > 1 && !overflow) {   // uniform
-        // the block's polynomial re-centred on every tile of the workgroup at once
-        const double inv_brho = 1.0 / brho;
-        for (int idx = threadIdx.x; idx < TPW * (kOrder + 1); idx += kThreads) {
-            const int t = t_begin + idx / (kOrder + 1), r = idx % (kOrder + 1);
-            double cx, cy, rho;
-            region(p, b_i + (int64_t)(t % L) * kTile, b_j + (int64_t)(t / L) * kTile, kTile, cx, cy, rho);
-            ex.B[t][r] = shift_coeff(ex.A, r, make_double2((cx - bcx) * inv_brho, (cy - bcy) * inv_brho),
-                                     rho * inv_brho);
-        }
-        __syncthreads();
-    }
+__constant__ FactorialTable kFactorial = make_factorials();
 
-    for (int t = t_begin; t < t_end; ++t) {   // uniform trip count
-        const int64_t tile_i = b_i + (int64_t)(t % L) * kTile;
-        const int64_t tile_j = b_j + (int64_t)(t / L) * kTile;
-        if (tile_i >= p.nx || tile_j >= p.ny) continue;   // uniform: no ray of this tile is in the lattice block
+// Re-centring.  A polynomial sum_q A_q s^q on s = a + b s' has the coefficients
+//   B_r = b^r sum_{q >= r} A_q C(q, r) a^(q - r)
+//       = (b^r / r!) sum_{j >= 0} alpha_{r + j} a^j / j!,  alpha_q = q! A_q,
+// and the last sum by Horner takes one complex multiply-add a step:
+//   S <- alpha_{r + j - 1} + (a / j) S,  j = kOrder - r ... 1.
+// (Scaling by factorials takes the binomials out of the loop; re-centring is
+// exact algebra, so no truncation enters beyond the coefficients dropped.)
+// alpha is zero past kOrder, so a step from any larger j is harmless.
+__device__ __forceinline__ double2 recentre_step(double2 S, double2 alpha, double ax, double ay) {
+    return make_double2(__builtin_fma(S.x, ax, __builtin_fma(-S.y, ay, alpha.x)),
+                        __builtin_fma(S.x, ay, __builtin_fma(S.y, ax, alpha.y)));
+}
 
-        const int(*near_idx)[kNearPerWave] = ex.outer_idx;
-        const int *near_n = ex.outer_n;
-        const double2 *coef = ex.B[L == 1 ? 0 : t];
-        double cx = bcx, cy = bcy, rho = brho;
-        if (L == 1 && !overflow) {   // uniform
-            // a copy per tile: read from a buffer the loop writes, the
-            // coefficients stay in LDS instead of 100 VGPRs
-            if (threadIdx.x <= kOrder) ex.B[0][threadIdx.x] = ex.A[threadIdx.x];
-            __syncthreads();
-        }
-        if (L > 1 && !overflow) {   // uniform
-            region_uniform(p, tile_i, tile_j, kTile, cx, cy, rho);
-            double2 acc[kOrder + 1];
-#pragma unroll
-            for (int q = 0; q <= kOrder; ++q) acc[q] = make_double2(0.0, 0.0);
-            const double r_near = rho * inv_theta;
-            const int n0 = ex.outer_n[0], n1 = n0 + ex.outer_n[1], n2 = n1 + ex.outer_n[2];
-            p2l_pass(
-                uniform(n_outer),
-                [&](int e, int &k, double &x, double &y, double &m) {
-                    k = e < n0   ? ex.outer_idx[0][e]
-                        : e < n1 ? ex.outer_idx[1][e - n0]
-                        : e < n2 ? ex.outer_idx[2][e - n1]
-                                 : ex.outer_idx[3][e - n2];
-                    x = st[k].x;
-                    y = st[k].y;
-                    m = st[k].m;
-                },
-                cx, cy, rho, uniform_f64(r_near * r_near), acc, ex.inner_idx, ex.inner_n);
-            reduce_coeffs<true>(acc, ex, ex.B[t]);   // its barriers also publish inner_n
-            near_idx = ex.inner_idx;
-            near_n = ex.inner_n;
-        }
+// 1 / q!.
+constexpr FactorialTable make_inverse_factorials() {
+    FactorialTable t = make_factorials();
+    for (int q = 0; q <= kOrder; ++q) t.f[q] = 1.0 / t.f[q];
+    return t;
+}
 
-        double tx[kCX], ty[kCY];
+__constant__ FactorialTable kInverseFactorial = make_inverse_factorials();
+
+// 1 / j (f[0] unused).
+constexpr FactorialTable make_inverses() {
+    FactorialTable t{};
+    t.f[0] = 0.0;
+    for (int q = 1; q <= kOrder; ++q) t.f[q] = 1.0 / q;
+    return t;
+}
+
+__constant__ FactorialTable kInverse = make_inverses();
+
+// Steps j = hi ... lo of the coefficients r0, r0 + 4, ... (the first N of
+// them; alpha points at alpha_r0).
+template <int N, int EACH>
+__device__ __forceinline__ void recentre_run(double2 (&S)[EACH], const double2 *alpha, double sx, double sy, int hi,
+                                             int lo) {
+#pragma unroll 2
+    for (int j = hi; j >= lo; --j) {
+        const double ax = sx * kInverse.f[j], ay = sy * kInverse.f[j];
 #pragma unroll
-        for (int a = 0; a < kCX; ++a) tx[a] = image_angle(p.x0, p.i0 + tile_i + lx + kLanesX * a, p.dx);
-#pragma unroll
-        for (int b = 0; b < kCY; ++b) ty[b] = image_angle(p.y0, p.j0 + tile_j + ly + kLanesY * b, p.dy);
-        double ax[kCY][kCX], ay[kCY][kCX];
-        if (!overflow) {
-            // far field: Horner in s = (z - c) / rho for the lane's rays
-            // together, one coefficient at a time (one LDS read each);
-            // f = alpha_x - i alpha_y is then added to the macro term
-            const double inv_rho = 1.0 / rho;
-            double wx[kCX], wy[kCY];
-#pragma unroll
-            for (int a = 0; a < kCX; ++a) wx[a] = (tx[a] - cx) * inv_rho;
-#pragma unroll
-            for (int b = 0; b < kCY; ++b) wy[b] = (ty[b] - cy) * inv_rho;
-            const double2 top = coef[kOrder];
-#pragma unroll
-            for (int b = 0; b < kCY; ++b)
-#pragma unroll
-                for (int a = 0; a < kCX; ++a) {
-                    ax[b][a] = top.x;
-                    ay[b][a] = top.y;
-                }
-            for (int q = kOrder - 1; q >= 0; --q) {
-                const double2 bq = coef[q];
-#pragma unroll
-                for (int b = 0; b < kCY; ++b)
-#pragma unroll
-                    for (int a = 0; a < kCX; ++a) {
-                        const double fx = ax[b][a], fy = ay[b][a];
-                        ax[b][a] = __builtin_fma(fx, wx[a], __builtin_fma(-fy, wy[b], bq.x));
-                        ay[b][a] = __builtin_fma(fx, wy[b], __builtin_fma(fy, wx[a], bq.y));
-                    }
-            }
-#pragma unroll
-            for (int b = 0; b < kCY; ++b)
-#pragma unroll
-                for (int a = 0; a < kCX; ++a) {
-                    double mx, my;
-                    macro_term(p, tx[a], ty[b], mx, my);
-                    ax[b][a] = mx + ax[b][a];
-                    ay[b][a] = my - ay[b][a];
-                }
-            // near stars, directly, in index order
-            for (int w = 0; w < kWaves; ++w) {
-                const int cnt = uniform(near_n[w]);
-                for (int i = 0; i < cnt; ++i) direct_star(st, uniform(near_idx[w][i]), tx, ty, ax, ay);
-            }
-        } else {
-            // too many near stars for the lists: every star directly
-#pragma unroll
-            for (int b = 0; b < kCY; ++b)
-#pragma unroll
-                for (int a = 0; a < kCX; ++a) macro_term(p, tx[a], ty[b], ax[b][a], ay[b][a]);
-            for (int k = 0; k < n; ++k) direct_star(st, k, tx, ty, ax, ay);
-        }
-        finish_tile<kCX, kCY, kWinX, kWinY, true>(p, sh, tx, ty, ax, ay, tile_i, tile_j, lx, ly);
-        __syncthreads();   // the bin window, red[], B and the inner lists are reused by the next tile
-        bin_shared_init(sh);
+        for (int i = 0; i < (N < EACH ? N : EACH); ++i) S[i] = recentre_step(S[i], alpha[kWaves * i + j - 1], ax, ay);
     }
 }
 
-// The block pass (with or without cells), then the tiles at three
-// workgroups per compute unit (measured faster than two at every star count
-// once the block pass is a kernel of its own), one row of a block's tiles
-// per workgroup: L times as many workgroups as blocks, so that the last
-// round of a launch is a small part of it (on the 8192^2 lattice of 16384
-// stars, 1024 workgroups of 16 tiles filled 1.33 rounds of 768; 4096 of 4
-// tiles run 11 % faster, and rows beat 2, 8 or 16 tiles per workgroup).
+__device__ __forceinline__ double int_pow(double b, int r) {
+    double t = 1.0;
+#pragma unroll
+    for (int bit = 0; bit < 5; ++bit) {   // r <= kOrder < 32
+        if (r & (1 << bit)) t *= b;
+        b *= b;
+    }
+    return t;
+}
+
+constexpr int kComputeUnits = 256;
+constexpr int kTilesPerGroup = 4;                        // tiles a workgroup evaluates, a wave re-tests one
+constexpr int kAlpha = kOrder + 1 + kOrder;              // coefficients and the zeros past them
+constexpr int kWinWords = kWinX * kWinY / 2;             // two 16-bit counts a word
+
+struct TileShared {
+    double2 block[kAlpha];                               // alpha of the block's polynomial
+    double2 tile[kTilesPerGroup][kAlpha];                // alpha of each tile's
+    double2 patch[kTilesPerGroup * kPatches][kPatchOrder + 1];
+    double patch_x[kTilesPerGroup * kPatches], patch_y[kTilesPerGroup * kPatches];   // centres
+    double patch_inv[kTilesPerGroup * kPatches];         // 1 / radius
+    unsigned win[2][kWinWords];                          // count windows, by turns
+    int near_idx[kTilesPerGroup][kTileNear];
+    int near_n[kTilesPerGroup];                          // more than kTileNear: every near star of the block
+};
+
+// Image angle of lattice index base + off, base and off given as doubles:
+// exactly image_angle's value (indices are below 2^53, so their sum is exact).
+__device__ __forceinline__ double image_angle_at(double origin, double base, int off, double step) {
+#pragma clang fp contract(off)
+    double t = (base + (double)off) + 0.5;
+    t = t * step;
+    return origin + t;
+}
+
+// A lane's rays: a column in each of two neighbouring patches, kRows rows.
+// (One patch at a time makes the stars' loads and loop 15 % slower; all four
+// of a tile's row spill at three workgroups a compute unit.)
+constexpr int kCols = 2;
+constexpr int kRows = kPatchRays / 64;
+
+// Star (sx, sy, sm) added to a lane's rays, one reciprocal for all eight (a
+// product tree with the mass at its root, as in the one-pass kernel; a ray
+// on the star turns all eight NaN, see expansion_tile_kernel).
+__device__ __forceinline__ void near_star(double sx, double sy, double sm, const double (&tx)[kCols],
+                                          const double (&ty)[kRows], double (&ax)[kCols][kRows],
+                                          double (&ay)[kCols][kRows]) {
+    double ey[kRows], ey2[kRows];
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        ey[k] = ty[k] - sy;
+        ey2[k] = ey[k] * ey[k];
+    }
+    double ex[kCols], r2[kCols * kRows], w[kCols * kRows];
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) {
+        ex[c] = tx[c] - sx;
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) r2[c * kRows + k] = __builtin_fma(ex[c], ex[c], ey2[k]);
+    }
+    scaled_reciprocals<kCols * kRows>(r2, sm, w);
+#pragma unroll
+    for (int c = 0; c < kCols; ++c)
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) {
+            ax[c][k] = __builtin_fma(w[c * kRows + k], ex[c], ax[c][k]);
+            ay[c][k] = __builtin_fma(w[c * kRows + k], ey[k], ay[c][k]);
+        }
+}
+
+// The stars a tile sums directly, one after the other, uniform in the wave:
+// all stars when the block's lists have overflowed, the block's near stars
+// (each wave's list of the block pass in turn) when the tile's list has, else
+// the tile's near stars; body(x, y, m).
+template <class Body>
+__device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, const ConstStar *st, const BlockFar *f,
+                                                bool all, int n_stars, Body body) {
+    const int cnt = all ? n_stars : uniform(sh.near_n[t]);
+    if (!all && cnt <= kTileNear) {
+        // 64 indices at a time in the lanes; the next star's record is loaded
+        // while the current one is summed
+        for (int i0 = 0; i0 < cnt; i0 += 64) {
+            const int m = cnt - i0 < 64 ? cnt - i0 : 64;
+            const int idx = sh.near_idx[t][i0 + threadIdx.x % 64];
+            int k = __builtin_amdgcn_readlane(idx, 0);
+            double sx = st[k].x, sy = st[k].y, sm = st[k].m;
+            for (int i = 0; i < m; ++i) {
+                asm volatile("" : "+s"(sx), "+s"(sy), "+s"(sm));   // the current record is here
+                k = __builtin_amdgcn_readlane(idx, i + 1 < m ? i + 1 : i);
+                const double nx = st[k].x, ny = st[k].y, nm = st[k].m;
+                __builtin_amdgcn_sched_barrier(0);                 // the loads stay ahead of the sum
+                body(sx, sy, sm);
+                sx = nx;
+                sy = ny;
+                sm = nm;
+            }
+        }
+        return;
+    }
+    if (all) {
+        for (int k = 0; k < cnt; ++k) body(st[k].x, st[k].y, st[k].m);
+        return;
+    }
+    for (int w = 0; w < kWaves; ++w) {
+        const int in_list = uniform(f->outer_n[w]);
+        for (int i = 0; i < in_list; ++i) {
+            const int k = uniform(f->outer_idx[w][i]);
+            body(st[k].x, st[k].y, st[k].m);
+        }
+    }
+}
+
+// The tiles of the blocks of L x L tiles, after the block pass.  Workgroup g
+// takes kTilesPerGroup tiles of block g / kSubs (for L = 4 a row of them, for
+// L = 2 the whole block, for L = 1 the one tile), in three phases:
+//   1. One wave per tile re-centres the block's polynomial on its tile,
+//      re-tests the block's near stars (far ones join the polynomial, near
+//      ones go to the tile's list) and sums the lanes' series.  A wave does
+//      this alone, without a barrier: with the four waves sharing each tile's
+//      stars, every wave still had to sum all 50 components, four times the
+//      work, between two barriers a tile.
+//   2. The tiles' polynomials are re-centred on their 16 patches of 16 x 16
+//      rays, keeping kPatchOrder terms.  A patch is a quarter of its tile
+//      across, so its terms fall four times as fast: a star farther than
+//      rho / theta from the tile's centre is at least (1 / theta - 0.77) rho
+//      from the patch's, whose radius is 0.239 rho, and what is dropped is below
+//      (0.239 / (1 / theta - 0.77))^14 / (1 - 0.08) of its term: 1.4e-16
+//      for theta = 0.25 and 4e-15 for 0.3, under the bounds of the tile's own
+//      truncation (1.5e-15, 1.6e-13).  13 instead of 24 multiply-adds a ray.
+//   3. Tile by tile, each wave evaluates four patches, four rays a lane: the
+//      polynomial by Horner, the near stars directly, the pixel, the count.
+//      Rays are counted as they come, in an LDS window around the pixel that
+//      the tile's centre maps to without the near stars, two 16-bit counts a
+//      word (a tile has 4096 rays); two windows take turns, so that a tile
+//      needs one barrier, after which its window is merged into the map while
+//      the next tile fills the other.
+// Bound by VALU issue: about 170 instructions a ray (52 Horner, 8.5 per near
+// star, 36 pixel and count, 15 for the first two phases), where 16 rays a lane
+// at order 24, each star's reciprocal a ray's own, took 273: 16384 stars and
+// 8192^2 rays 650 -> 405 us; the share of the chip's FP64 issue rate is alike.
+// Three workgroups a compute unit: at four the registers spill.
+// MAP: counts only, with pixel_coordinate's form of the division (the usual
+// call); otherwise also the per-ray outputs, and the division where needed.
+template <int L, int G, bool MAP>
+__global__ __launch_bounds__(kThreads, 3) void expansion_tile_kernel(ShootParams p, double theta_open, int blocks_x,
+                                                                     int skew, const BlockFar *__restrict__ far) {
+    static_assert(G == 1 || (G == kTilesPerGroup && L > 1), "one tile or a group");
+    constexpr int kSubs = L * L / G;
+    __shared__ TileShared sh;
+    const int lane = threadIdx.x % 64, wave = uniform(threadIdx.x / 64);
+    const int pw = skew >= 0 ? 16 >> skew : 16 << -skew, ph = kPatchRays / pw;   // patch
+    const int tw = kPatchSide * pw, th = kPatchSide * ph;                        // tile
+    const int blk = (int)(blockIdx.x / kSubs), t_begin = (int)(blockIdx.x % kSubs) * G;
+    const int64_t b_i = (int64_t)(blk % blocks_x) * (tw * L);
+    const int64_t b_j = (int64_t)(blk / blocks_x) * (th * L);
+    const ConstStar *st = const_stars(uniform_ptr(p.stars));
+    const BlockFar *f = far + blk;
+    const int n = uniform(p.n_stars);
+    const double inv_theta = uniform_f64(1.0 / theta_open);
+
+    bool overflow = false;
+    int n_outer = 0, before[kWaves];   // the block's near stars, and those of earlier lists
+    for (int w = 0; w < kWaves; ++w) {
+        const int cnt = uniform(f->outer_n[w]);
+        before[w] = n_outer;
+        n_outer += cnt;
+        overflow |= cnt > kNearPerWave;
+    }
+    for (int e = threadIdx.x; e < 2 * kWinWords; e += kThreads) sh.win[0][e] = 0;
+    if (threadIdx.x < kAlpha) {
+        double2 v = make_double2(0.0, 0.0);
+        if (threadIdx.x <= kOrder) {
+            const double fq = kFactorial.f[threadIdx.x];
+            v = make_double2(f->A[threadIdx.x].x * fq, f->A[threadIdx.x].y * fq);
+        }
+        (L == 1 ? sh.tile[0] : sh.block)[threadIdx.x] = v;
+    }
+    __syncthreads();
+
+    // --- phase 1
+    if (L == 1) {
+        // the block is the tile: its near stars, in one list
+        if (threadIdx.x == 0) sh.near_n[0] = n_outer;
+        if (!overflow && n_outer <= kTileNear)
+            for (int w = 0; w < kWaves; ++w)
+                for (int i = threadIdx.x; i < uniform(f->outer_n[w]); i += kThreads)
+                    sh.near_idx[0][before[w] + i] = f->outer_idx[w][i];
+    } else if (!overflow && wave < G) {
+        const int t = t_begin + wave;
+        double bcx, bcy, brho, cx, cy, rho;
+        region_uniform(p, b_i, b_j, tw * L, th * L, bcx, bcy, brho);
+        region_uniform(p, b_i + (int64_t)(t % L) * tw, b_j + (int64_t)(t / L) * th, tw, th, cx, cy, rho);
+        const double r_near = rho * inv_theta, r_near2 = uniform_f64(r_near * r_near);
+        double2 acc[kOrder + 1];
+#pragma unroll
+        for (int q = 0; q <= kOrder; ++q) acc[q] = make_double2(0.0, 0.0);
+        int found = 0;   // near stars so far (uniform in the wave)
+        for (int base = 0; base < n_outer; base += 64) {
+            const int e = base + lane;
+            bool near = false;
+            int k = 0;
+            if (e < n_outer) {
+                const int w = (e >= before[1]) + (e >= before[2]) + (e >= before[3]);
+                k = f->outer_idx[w][e - (w == 0 ? 0 : w == 1 ? before[1] : w == 2 ? before[2] : before[3])];
+                const double sx = st[k].x, sy = st[k].y, sm = st[k].m;
+                const double dx = cx - sx, dy = cy - sy;
+                const double d2 = dx * dx + dy * dy;
+                near = d2 <= r_near2;
+                if (!near) {
+                    const double inv = 1.0 / d2;
+                    const double2 u = make_double2(dx * inv, -dy * inv);        // 1 / (c - z_k)
+                    const double2 mu = make_double2(-u.x * rho, -u.y * rho);    // -u rho
+                    double2 tq = make_double2(sm * u.x, sm * u.y);              // m u
+#pragma unroll
+                    for (int q = 0; q <= kOrder; ++q) {
+                        acc[q].x += tq.x;
+                        acc[q].y += tq.y;
+                        if (q < kOrder) tq = cmul(tq, mu);
+                    }
+                }
+            }
+            const unsigned long long ball = __ballot(near);
+            if (near) {
+                const int pos = found + __popcll(ball & ((1ull << lane) - 1ull));
+                if (pos < kTileNear) sh.near_idx[wave][pos] = k;
+            }
+            found += __popcll(ball);
+        }
+        if (lane == 0) sh.near_n[wave] = found;
+        const double v = wave_reduce_coeffs(acc);
+        // the block's polynomial re-centred: lane r takes coefficient r
+        const double inv_brho = 1.0 / brho;
+        const double sx = (cx - bcx) * inv_brho, sy = (cy - bcy) * inv_brho;
+        const int r = lane <= kOrder ? lane : kOrder;
+        double2 S = sh.block[r + kOrder];
+#pragma unroll 4
+        for (int j = kOrder; j >= 1; --j)
+            S = recentre_step(S, sh.block[r + j - 1], sx * kInverse.f[j], sy * kInverse.f[j]);
+        const double br = int_pow(rho * inv_brho, r);
+        if (lane < kAlpha) sh.tile[wave][lane] = lane <= kOrder ? make_double2(S.x * br, S.y * br) : make_double2(0.0, 0.0);
+        // plus the re-tested far stars', unless the list has overflowed: then
+        // the block's near stars are all summed directly
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the stores above, by other lanes
+        __builtin_amdgcn_wave_barrier();
+        if (found <= kTileNear && lane < 2 * (kOrder + 1)) {
+            double *d = reinterpret_cast<double *>(sh.tile[wave]);
+            d[lane] += v * kFactorial.f[lane / 2];
+        }
+    }
+    __syncthreads();
+
+    // --- phase 2: lane = (tile, patch), the waves share the coefficients:
+    // wave w takes r = w, w + 4, ... (with one tile, lane group i of 16 takes
+    // r = w + 4 i)
+    if (!overflow) {   // uniform
+        constexpr int kEach = G == 1 ? 1 : (kPatchOrder + kWaves) / kWaves;
+        const int pt = lane % kPatches, id = G == 1 ? pt : lane;
+        const int g = G == 1 ? 0 : lane / kPatches, r0 = wave + (G == 1 ? kWaves * (lane / kPatches) : 0);
+        const int t = t_begin + g;
+        const int64_t ti = b_i + (int64_t)(t % L) * tw, tj = b_j + (int64_t)(t / L) * th;
+        double cx, cy, rho, qx, qy, qrho;
+        region(p, ti, tj, tw, th, cx, cy, rho);
+        region(p, ti + (pt % kPatchSide) * pw, tj + (pt / kPatchSide) * ph, pw, ph, qx, qy, qrho);
+        const double inv_rho = 1.0 / rho;
+        const double sx = (qx - cx) * inv_rho, sy = (qy - cy) * inv_rho, b = qrho * inv_rho;
+        double2 S[kEach];
+        const double2 *alpha = sh.tile[g] + r0;
+#pragma unroll
+        for (int i = 0; i < kEach; ++i) S[i] = alpha[kOrder];   // the term j = kOrder - 4 i (zero unless r0 = 0)
+        // coefficient r = r0 + 4 i has terms up to j = kOrder - r
+        recentre_run<1, kEach>(S, alpha, sx, sy, kOrder, kOrder - kWaves + 1);
+        recentre_run<2, kEach>(S, alpha, sx, sy, kOrder - kWaves, kOrder - 2 * kWaves + 1);
+        recentre_run<3, kEach>(S, alpha, sx, sy, kOrder - 2 * kWaves, kOrder - 3 * kWaves + 1);
+        recentre_run<4, kEach>(S, alpha, sx, sy, kOrder - 3 * kWaves, 1);
+#pragma unroll
+        for (int i = 0; i < kEach; ++i) {
+            const int r = r0 + kWaves * i;
+            if (r <= kPatchOrder) {
+                const double c = int_pow(b, r) * kInverseFactorial.f[r];
+                sh.patch[id][r] = make_double2(S[i].x * c, S[i].y * c);
+            }
+        }
+        if (r0 == 0) {
+            sh.patch_x[id] = qx;
+            sh.patch_y[id] = qy;
+            sh.patch_inv[id] = 1.0 / qrho;
+        }
+    }
+    __syncthreads();
+
+    // --- phase 3
+    const int lx = lane & (pw - 1), ly = lane / pw, dj = 64 / pw;   // a lane's rays are dj rows apart
+    int binned = 0;   // this lane's rays in the source window
+    int turn = 0;     // of the windows: only tiles that are evaluated take one
+    for (int g = 0; g < G; ++g) {   // uniform trip count
+        const int t = t_begin + g;
+        const int64_t tile_i = b_i + (int64_t)(t % L) * tw, tile_j = b_j + (int64_t)(t / L) * th;
+        if (tile_i >= p.nx || tile_j >= p.ny) continue;   // uniform: no ray of this tile is in the lattice block
+        const int left = uniform((int)(p.nx - tile_i < tw ? p.nx - tile_i : tw));
+        const int down = uniform((int)(p.ny - tile_j < th ? p.ny - tile_j : th));
+        const double base_i = uniform_f64((double)(p.i0 + tile_i)), base_j = uniform_f64((double)(p.j0 + tile_j));
+        unsigned *win = sh.win[turn];
+        turn ^= 1;
+        // the window's corner, from the tile's centre (its own polynomial's first coefficient)
+        int ox, oy;
+        {
+            double cx, cy, rho, mx, my, c0x = 0.0, c0y = 0.0;
+            region_uniform(p, tile_i, tile_j, tw, th, cx, cy, rho);
+            if (!overflow) {
+                c0x = sh.tile[g][0].x;
+                c0y = sh.tile[g][0].y;
+            }
+            macro_term(p, cx, cy, mx, my);
+            const double u = (cx - (mx + c0x) - p.X0) * p.ipx, v = (cy - (my - c0y) - p.Y0) * p.ipy;
+            ox = uniform((int)fmin(fmax(u, -1e9), 1e9)) - kWinX / 2;   // (NaN: -1e9)
+            oy = uniform((int)fmin(fmax(v, -1e9), 1e9)) - kWinY / 2;
+        }
+        // the wave's row of patches: rows pj ... pj + ph - 1 of the tile
+        const int pj = wave * ph;
+#pragma unroll 1
+        for (int q0 = 0; q0 < kPatchSide; q0 += kCols) {
+            const int pi = q0 * pw, pid0 = g * kPatches + wave * kPatchSide + q0;
+            if (pi >= left || pj >= down) continue;   // uniform
+            double tx[kCols], ty[kRows], ax[kCols][kRows], ay[kCols][kRows];
+#pragma unroll
+            for (int c = 0; c < kCols; ++c) tx[c] = image_angle_at(p.x0, base_i, pi + c * pw + lx, p.dx);
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) ty[k] = image_angle_at(p.y0, base_j, pj + ly + dj * k, p.dy);
+#pragma unroll
+            for (int c = 0; c < kCols; ++c) {
+                // far field: Horner in s = (z - c) / rho; f = alpha_x - i alpha_y is
+                // then added to the macro term
+                double fx[kRows], fy[kRows];
+                if (!overflow) {
+                    const int pid = pid0 + c;
+                    const double inv_rho = sh.patch_inv[pid], py = sh.patch_y[pid];
+                    const double wx = (tx[c] - sh.patch_x[pid]) * inv_rho;
+                    double wy[kRows];
+                    const double2 top = sh.patch[pid][kPatchOrder];
+#pragma unroll
+                    for (int k = 0; k < kRows; ++k) {
+                        wy[k] = (ty[k] - py) * inv_rho;
+                        fx[k] = top.x;
+                        fy[k] = top.y;
+                    }
+#pragma unroll
+                    for (int r = kPatchOrder - 1; r >= 0; --r) {
+                        const double2 b = sh.patch[pid][r];
+#pragma unroll
+                        for (int k = 0; k < kRows; ++k) {
+                            const double hx = fx[k], hy = fy[k];
+                            fx[k] = __builtin_fma(hx, wx, __builtin_fma(-hy, wy[k], b.x));
+                            fy[k] = __builtin_fma(hx, wy[k], __builtin_fma(hy, wx, b.y));
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < kRows; ++k) fx[k] = fy[k] = 0.0;
+                }
+#pragma unroll
+                for (int k = 0; k < kRows; ++k) {
+                    double mx, my;
+                    macro_term(p, tx[c], ty[k], mx, my);
+                    ax[c][k] = mx + fx[k];
+                    ay[c][k] = my - fy[k];
+                }
+            }
+            for_tile_direct(sh, g, st, f, overflow, n,
+                            [&](double sx, double sy, double sm) { near_star(sx, sy, sm, tx, ty, ax, ay); });
+            bool bad = false;
+#pragma unroll
+            for (int c = 0; c < kCols; ++c)
+#pragma unroll
+                for (int k = 0; k < kRows; ++k) bad |= !__builtin_isfinite(ax[c][k] + ay[c][k]);
+            if (__builtin_amdgcn_ballot_w64(bad) != 0) {   // uniform: a ray on a star, or far out of range
+                // the rays with such sums again, one by one, a division a star;
+                // through private arrays, so that this cold path takes no
+                // registers of the rest
+                double sum[2][kCols * kRows];
+#pragma unroll
+                for (int c = 0; c < kCols; ++c)
+#pragma unroll
+                    for (int k = 0; k < kRows; ++k) {
+                        sum[0][c * kRows + k] = ax[c][k];
+                        sum[1][c * kRows + k] = ay[c][k];
+                    }
+#pragma unroll 1
+                for (int q = 0; q < kCols * kRows; ++q) {
+                    const bool again = !__builtin_isfinite(sum[0][q]) || !__builtin_isfinite(sum[1][q]);
+                    if (__builtin_amdgcn_ballot_w64(again) == 0) continue;   // uniform
+                    const int c = q / kRows, k = q % kRows, pid = pid0 + c;
+                    const double x = image_angle_at(p.x0, base_i, pi + c * pw + lx, p.dx);
+                    const double y = image_angle_at(p.y0, base_j, pj + ly + dj * k, p.dy);
+                    double fx = 0.0, fy = 0.0, mx, my;
+                    if (!overflow) {
+                        const double inv_rho = sh.patch_inv[pid];
+                        const double wx = (x - sh.patch_x[pid]) * inv_rho, wy = (y - sh.patch_y[pid]) * inv_rho;
+#pragma unroll 1
+                        for (int r = kPatchOrder; r >= 0; --r) {
+                            const double2 b = sh.patch[pid][r];
+                            const double hx = fx, hy = fy;
+                            fx = __builtin_fma(hx, wx, __builtin_fma(-hy, wy, b.x));
+                            fy = __builtin_fma(hx, wy, __builtin_fma(hy, wx, b.y));
+                        }
+                    }
+                    macro_term(p, x, y, mx, my);
+                    double sxx = mx + fx, syy = my - fy;
+                    for_tile_direct(sh, g, st, f, overflow, n, [&](double sx, double sy, double sm) {
+                        const double ex = x - sx, ey = y - sy;
+                        const double w = sm / __builtin_fma(ex, ex, ey * ey);
+                        sxx = __builtin_fma(w, ex, sxx);
+                        syy = __builtin_fma(w, ey, syy);
+                    });
+                    if (again) {
+                        sum[0][q] = sxx;
+                        sum[1][q] = syy;
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < kCols; ++c)
+#pragma unroll
+                    for (int k = 0; k < kRows; ++k) {
+                        ax[c][k] = sum[0][c * kRows + k];
+                        ay[c][k] = sum[1][c * kRows + k];
+                    }
+            }
+            // Eq. (2), the pixel, the count
+#pragma unroll
+            for (int c = 0; c < kCols; ++c) {
+                const int i = pi + c * pw + lx;
+                int32_t is[kRows], js[kRows];
+                {
+#pragma clang fp contract(off)
+                    if (MAP || p.fast_pixels) {   // uniform
+#pragma unroll
+                        for (int k = 0; k < kRows; ++k)
+                            window_pixel(p, pixel_coordinate(tx[c] - ax[c][k], p.X0, p.Px, p.ipx),
+                                         pixel_coordinate(ty[k] - ay[c][k], p.Y0, p.Py, p.ipy), is[k], js[k]);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < kRows; ++k)
+                            window_pixel(p, ((tx[c] - ax[c][k]) - p.X0) / p.Px, ((ty[k] - ay[c][k]) - p.Y0) / p.Py,
+                                         is[k], js[k]);
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < kRows; ++k) {
+                    const bool mine = i < left && pj + ly + dj * k < down;
+                    if (!MAP && mine) {
+                        const int64_t o = (tile_j + pj + ly + dj * k) * p.nx + tile_i + i;
+                        if (p.beta_x) p.beta_x[o] = tx[c] - ax[c][k];
+                        if (p.beta_y) p.beta_y[o] = ty[k] - ay[c][k];
+                        if (p.bin) p.bin[o] = is[k] < 0 ? -1 : js[k] * p.NX + is[k];
+                    }
+                    if (!mine || (!MAP && !p.counts)) is[k] = -1;
+                    const unsigned ux = (unsigned)(is[k] - ox), uy = (unsigned)(js[k] - oy);
+                    const bool in = is[k] >= 0, in_win = ux < (unsigned)kWinX && uy < (unsigned)kWinY;
+                    binned += in ? 1 : 0;
+                    if (in && in_win) atomicAdd(&win[(uy * kWinX + ux) / 2], ux % 2 ? 0x10000u : 1u);
+                    if (in && !in_win) atomicAdd(&p.counts[js[k] * p.NX + is[k]], 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);   // keep the columns' temporaries apart
+            }
+        }
+        if (!MAP && !p.counts) continue;   // uniform
+        __syncthreads();   // the window is complete; the one before it has been merged
+        // a wave per row of the window, 8 rows read ahead of their tests
+        const int gx = ox + lane, half = lane % 2 * 16;
+        const bool in_map = gx >= 0 && gx < p.NX;
+#pragma unroll 1
+        for (int r0 = 0; r0 < kWinY / kWaves; r0 += 8) {
+            unsigned v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = win[(((r0 + u) * kWaves + wave) * kWinX + lane) / 2];
+            if (__builtin_amdgcn_ballot_w64((v[0] | v[1] | v[2] | v[3] | v[4] | v[5] | v[6] | v[7]) != 0) == 0)
+                continue;   // uniform: eight empty rows
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (v[u]) {
+                    const int wy = (r0 + u) * kWaves + wave, gy = oy + wy;
+                    win[(wy * kWinX + lane) / 2] = 0;
+                    const int cnt = (int)(v[u] >> half & 0xFFFFu);
+                    if (cnt && in_map && gy >= 0 && gy < p.NY) atomicAdd(&p.counts[gy * p.NX + gx], cnt);
+                }
+            }
+        }
+    }
+    if (p.n_binned) {   // uniform
+        const long long all = wave_sum((long long)binned);
+        if (lane == 0 && all) atomicAdd(p.n_binned, (unsigned long long)all);
+    }
+}
+
+// The block pass (with or without cells), then the tiles: kTilesPerGroup a
+// workgroup when that leaves every compute unit four workgroups, else one
+// (2048^2 rays: 58 us against 72).
 template <int L>
-hipError_t launch_level(const ShootParams &p, const StarCells &cells, double theta_open, int64_t tiles_x,
-                        int64_t tiles_y, BlockFar *far, hipStream_t s) {
-    const int64_t bx = (tiles_x + L - 1) / L, by = (tiles_y + L - 1) / L;
+hipError_t launch_level(const ShootParams &p, const StarCells &cells, double theta_open, const TileGrid &g,
+                        BlockFar *far, hipStream_t s) {
+    const int64_t bx = (g.tiles_x + L - 1) / L, by = (g.tiles_y + L - 1) / L;
     const dim3 grid((unsigned)(bx * by));
     if (cells.ncx > 0)
         hipLaunchKernelGGL(expansion_block_kernel<true>, grid, dim3(kThreads), 0, s, p, cells, theta_open, (int)bx,
-                           kTile * L, far);
+                           g.w * L, g.h * L, far);
     else
         hipLaunchKernelGGL(expansion_block_kernel<false>, grid, dim3(kThreads), 0, s, p, cells, theta_open, (int)bx,
-                           kTile * L, far);
-    hipLaunchKernelGGL((expansion_fp64_kernel<L, L, 3>), dim3((unsigned)(bx * by * L)), dim3(kThreads), 0, s, p,
-                       theta_open, (int)bx, far);
+                           g.w * L, g.h * L, far);
+    const bool map = p.counts && p.fast_pixels && !p.beta_x && !p.beta_y && !p.bin;
+    if constexpr (L > 1) {
+        const int64_t groups = bx * by * (L * L / kTilesPerGroup);
+        if (groups >= 4 * kComputeUnits) {
+            if (map)
+                hipLaunchKernelGGL((expansion_tile_kernel<L, kTilesPerGroup, true>), dim3((unsigned)groups),
+                                   dim3(kThreads), 0, s, p, theta_open, (int)bx, g.skew, far);
+            else
+                hipLaunchKernelGGL((expansion_tile_kernel<L, kTilesPerGroup, false>), dim3((unsigned)groups),
+                                   dim3(kThreads), 0, s, p, theta_open, (int)bx, g.skew, far);
+            return hipGetLastError();
+        }
+    }
+    const dim3 tiles((unsigned)(bx * by * L * L));
+    if (map)
+        hipLaunchKernelGGL((expansion_tile_kernel<L, 1, true>), tiles, dim3(kThreads), 0, s, p, theta_open, (int)bx,
+                           g.skew, far);
+    else
+        hipLaunchKernelGGL((expansion_tile_kernel<L, 1, false>), tiles, dim3(kThreads), 0, s, p, theta_open, (int)bx,
+                           g.skew, far);
     return hipGetLastError();
 }
 
@@ -672,13 +1053,12 @@ int expansion_order() { return kOrder; }
 // lists (then its tiles sum every star directly).  Counting the tile
 // workgroups as separate work picked 4 x 4 blocks for the 4096^2-ray maps
 // of 512 to 50 000 stars, five times slower than 2 x 2.
-int expansion_block(int64_t nx, int64_t ny, int64_t n_stars, int n_cu) {
-    const int64_t tx = (nx + kTile - 1) / kTile, ty = (ny + kTile - 1) / kTile;
+int expansion_block(const TileGrid &g, int64_t n_stars, int n_cu) {
     const int64_t slots = 3 * (int64_t)(n_cu > 0 ? n_cu : 256);
     int best = 1;
     double best_cost = 0.0;
     for (int L : {1, 2, 4}) {
-        const int64_t blocks = ((tx + L - 1) / L) * ((ty + L - 1) / L);
+        const int64_t blocks = ((g.tiles_x + L - 1) / L) * ((g.tiles_y + L - 1) / L);
         const double rounds = std::max(1.0, (double)blocks / (double)slots);   // a part-filled round runs faster
         const double cost = rounds * ((double)n_stars + 16384.0 * L * L);
         if (L == 1 || cost < best_cost) {
@@ -689,23 +1069,31 @@ int expansion_block(int64_t nx, int64_t ny, int64_t n_stars, int n_cu) {
     return best;
 }
 
-size_t expansion_workspace_bytes(int64_t nx, int64_t ny, int block) {
-    const int64_t tiles_x = (nx + kTile - 1) / kTile, tiles_y = (ny + kTile - 1) / kTile;
-    const int64_t blocks = ((tiles_x + block - 1) / block) * ((tiles_y + block - 1) / block);
+// 64 / 2^k by 64 * 2^k rays with k nearest to half the logarithm of dx / dy,
+// so that the sides differ by a factor of sqrt(2) at most (|k| <= kMaxSkew).
+TileGrid expansion_tiles(int64_t nx, int64_t ny, double dx, double dy) {
+    TileGrid g;
+    const double k = std::round(0.5 * std::log2(dx / dy));
+    g.skew = k >= kMaxSkew ? kMaxSkew : k <= -kMaxSkew ? -kMaxSkew : (int)k;   // (dx / dy may be 0 or infinite)
+    g.w = g.skew >= 0 ? 64 >> g.skew : 64 << -g.skew;
+    g.h = kPatchRays * kPatches / g.w;
+    g.tiles_x = (nx + g.w - 1) / g.w;
+    g.tiles_y = (ny + g.h - 1) / g.h;
+    return g;
+}
+
+size_t expansion_workspace_bytes(const TileGrid &g, int block) {
+    const int64_t blocks = ((g.tiles_x + block - 1) / block) * ((g.tiles_y + block - 1) / block);
     return (size_t)blocks * sizeof(BlockFar);
 }
 
-hipError_t launch_shoot_expansion(const ShootParams &p, const StarCells &cells, double theta_open, int block,
-                                  void *workspace, hipStream_t s) {
-    ShootParams q = p;
-    const int64_t tiles_x = (p.nx + kTile - 1) / kTile;
-    const int64_t tiles_y = (p.ny + kTile - 1) / kTile;
-    q.tiles_x = (int32_t)tiles_x;
+hipError_t launch_shoot_expansion(const ShootParams &p, const StarCells &cells, double theta_open, const TileGrid &g,
+                                  int block, void *workspace, hipStream_t s) {
     BlockFar *far = static_cast<BlockFar *>(workspace);
     switch (block) {
-        case 1: return launch_level<1>(q, cells, theta_open, tiles_x, tiles_y, far, s);
-        case 2: return launch_level<2>(q, cells, theta_open, tiles_x, tiles_y, far, s);
-        case 4: return launch_level<4>(q, cells, theta_open, tiles_x, tiles_y, far, s);
+        case 1: return launch_level<1>(p, cells, theta_open, g, far, s);
+        case 2: return launch_level<2>(p, cells, theta_open, g, far, s);
+        case 4: return launch_level<4>(p, cells, theta_open, g, far, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -25,7 +25,7 @@ KERNEL_SOURCES = {
     "batch_fp32_kernel": ["csrc/shoot_fp32.hip", "csrc/ray_common.h", "csrc/raysh_internal.h"],
     "partial_fp64_kernel": ["csrc/shoot_fp64.hip", "csrc/ray_common.h", "csrc/raysh_internal.h"],
     "finish_fp64_kernel": ["csrc/shoot_fp64.hip", "csrc/ray_common.h", "csrc/raysh_internal.h"],
-    "expansion_fp64_kernel": ["csrc/shoot_expansion.hip", "csrc/ray_common.h", "csrc/raysh_internal.h"],
+    "expansion_tile_kernel": ["csrc/shoot_expansion.hip", "csrc/ray_common.h", "csrc/raysh_internal.h"],
     "expansion_block_kernel": ["csrc/shoot_expansion.hip", "csrc/ray_common.h", "csrc/raysh_internal.h"],
     "light_curve_kernel": ["csrc/light_curves.hip", "csrc/smooth.h"],
     "light_curve_track_kernel": ["csrc/light_curves.hip", "csrc/smooth.h"],
