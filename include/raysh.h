@@ -164,7 +164,10 @@ int64_t raysh_n_stars(const raysh_ctx *ctx);
  * raysh_set_tile means min(share, 4)).  RAYSH_FP32_BULK: `star_tile` stars
  * are staged in LDS per pass (the FP32 partial sums are flushed into FP64
  * after each pass), and `share` must be 0.  EINVAL if the shape is not
- * compiled into the library.
+ * compiled into the library.  Until raysh_set_tile sets a RAYSH_FP64 shape,
+ * lattices that would leave compute units idle in the context's shape run in
+ * a form in which a workgroup's 4 to 16 waves share one tile and split its
+ * stars into contiguous runs, added in order after the macro term.
  */
 int raysh_set_tile(raysh_ctx *ctx, int precision, int cx, int cy, int share, int star_tile);
 

@@ -71,6 +71,11 @@ hipError_t bind_scratch(int device, void **out) {
     return hipSuccess;
 }
 
+hipError_t launch_one_pass(const raysh_ctx *c, const ShootParams &p) {
+    return c->fixed_shape ? raysh::launch_shoot_fp64(p, c->shape[0], c->stream)
+                          : raysh::launch_shoot_fp64_auto(p, c->shape[0], c->n_cu, c->stream);
+}
+
 int launch(raysh_ctx *c, const ShootParams &p, int precision, const char *what) {
     hipError_t e;
     if (precision == RAYSH_FP64) {
@@ -93,7 +98,7 @@ int launch(raysh_ctx *c, const ShootParams &p, int precision, const char *what) 
             }
             e = raysh::launch_split_fp64(p, c->shape[0], parts, c->d_partial, c->stream);
         } else {
-            e = raysh::launch_shoot_fp64(p, c->shape[0], c->stream);
+            e = launch_one_pass(c, p);
         }
     } else if (precision == RAYSH_FP32_BULK) {
         e = raysh::launch_shoot_fp32(p, c->shape[1], c->stream);
@@ -474,6 +479,7 @@ int raysh_set_tile(raysh_ctx *ctx, int precision, int cx, int cy, int share, int
         return set_error(RAYSH_EINVAL, "tile shape (%d, %d, %d, %d) is not built for precision %d", cx, cy,
                     share, star_tile, precision);
     ctx->shape[precision] = t;
+    if (precision == RAYSH_FP64) ctx->fixed_shape = true;
     return set_ok();
 }
 
@@ -598,7 +604,7 @@ int raysh_map_split_noalloc(raysh_ctx *ctx, const raysh_rays *rays, const raysh_
     hipError_t e = bind_scratch(ctx->device, &ptr);   // resolved by raysh_init; no allocation here
     if (e != hipSuccess) return hip_error(e, "raysh_map_split_noalloc");
     e = use > 1 ? raysh::launch_split_fp64(p, ctx->shape[0], use, static_cast<double2 *>(ptr), ctx->stream)
-                : raysh::launch_shoot_fp64(p, ctx->shape[0], ctx->stream);
+                : launch_one_pass(ctx, p);
     if (e != hipSuccess) return hip_error(e, "raysh_map_split_noalloc");
     return set_ok();
 }

@@ -18,6 +18,7 @@ struct raysh_ctx {
     unsigned long long *h_counter = nullptr;   // pinned
     // default launch shapes: the fastest on MI355X for the 16384-star workload
     raysh::TileShape shape[2] = {{8, 4, 16, 1}, {4, 4, 0, 128}};
+    bool fixed_shape = false;              // FP64 one pass: shape[0] whatever the lattice (raysh_set_tile)
     int star_parts = 1;                    // FP64 split of each ray's star sum (0 = automatic)
     double theta_open = 0.25;              // far-star criterion of RAYSH_FP64_EXPANSION
     int expansion_block = 0;               // tiles per side of its workgroups (0 = automatic)

@@ -68,6 +68,9 @@ struct TileShape {
 // Launchers (shoot_fp64.hip, shoot_fp32.hip).  Return hipSuccess or the
 // launch error; `shape` must be one the launcher supports.
 hipError_t launch_shoot_fp64(const ShootParams &p, const TileShape &shape, hipStream_t s);
+// ... or, for a lattice too small to fill the n_cu compute units in `shape`, with
+// the waves of a workgroup sharing a tile.
+hipError_t launch_shoot_fp64_auto(const ShootParams &p, const TileShape &shape, int n_cu, hipStream_t s);
 hipError_t launch_shoot_fp32(const ShootParams &p, const TileShape &shape, hipStream_t s);
 bool fp64_shape_supported(const TileShape &shape);
 // Compiled shapes: writes up to cap of them, returns how many exist.

@@ -287,6 +287,186 @@ __global__ __launch_bounds__(kThreads, 2) void shoot_fp64_kernel(ShootParams p) 
     fp64_tile<CX, CY, SHARE, NS>(p, sh, blockIdx.x);
 }
 
+// Sum of a float over the wave, in lane 63 (other lanes: partial sums).
+__device__ __forceinline__ float wave_sum_last(float v) {
+#define RAYSH_DPP_ADD(ctrl, rows) \
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, rows, 0xf, false))
+    RAYSH_DPP_ADD(0x111, 0xf);   // row_shr 1, 2, 4, 8: lane 15 of each row of 16
+    RAYSH_DPP_ADD(0x112, 0xf);
+    RAYSH_DPP_ADD(0x114, 0xf);
+    RAYSH_DPP_ADD(0x118, 0xf);
+    RAYSH_DPP_ADD(0x142, 0xa);   // row_bcast 15 into rows 1 and 3
+    RAYSH_DPP_ADD(0x143, 0xc);   // row_bcast 31 into rows 2 and 3
+#undef RAYSH_DPP_ADD
+    return v;
+}
+
+template <int W>
+struct WavesBin {
+    int win[kWinY * kWinX];
+    float red[W][3];   // each wave's sums of is, of js, and of rays binned
+};
+
+// finish_tile for waves_fp64_kernel: lanes 8 x 8, CX x CY rays a lane
+// (none that counts unless `mine`), W waves.  Nothing of a larger tile's sum is
+// alive here, so the pixels take pixel_coordinate's form, the mean pixel its
+// wave sums from DPP adds (it only places the window: floats will do), and
+// the merge reads rows ahead of their tests.
+template <int CX, int CY, int W>
+__device__ __forceinline__ void finish_waves(const ShootParams &p, WavesBin<W> &sh, bool mine,
+                                             const double (&tx)[CX], const double (&ty)[CY],
+                                             const double (&ax)[CY][CX], const double (&ay)[CY][CX],
+                                             int64_t tile_i, int64_t tile_j, int lane, int wave) {
+    int32_t is[CY][CX], js[CY][CX];
+    float s_is = 0.0f, s_js = 0.0f, s_n = 0.0f;
+#pragma unroll
+    for (int b = 0; b < CY; ++b)
+#pragma unroll
+        for (int a = 0; a < CX; ++a) {
+#pragma clang fp contract(off)
+            const double bx = tx[a] - ax[b][a], by = ty[b] - ay[b][a];
+            if (p.fast_pixels)   // uniform
+                window_pixel(p, pixel_coordinate(bx, p.X0, p.Px, p.ipx), pixel_coordinate(by, p.Y0, p.Py, p.ipy),
+                             is[b][a], js[b][a]);
+            else
+                window_pixel(p, (bx - p.X0) / p.Px, (by - p.Y0) / p.Py, is[b][a], js[b][a]);
+            const int64_t i = tile_i + lane % 8 + 8 * a, j = tile_j + lane / 8 + 8 * b;
+            if (mine && i < p.nx && j < p.ny) {
+                const int64_t o = j * p.nx + i;
+                if (p.beta_x) p.beta_x[o] = bx;
+                if (p.beta_y) p.beta_y[o] = by;
+                if (p.bin) p.bin[o] = is[b][a] < 0 ? -1 : js[b][a] * p.NX + is[b][a];
+            } else {
+                is[b][a] = -1;
+            }
+            if (is[b][a] >= 0) {
+                s_is += (float)is[b][a];
+                s_js += (float)js[b][a];
+                s_n += 1.0f;
+            }
+        }
+    if (!p.counts) return;   // uniform: no barrier is skipped by part of the group
+    s_is = wave_sum_last(s_is);
+    s_js = wave_sum_last(s_js);
+    s_n = wave_sum_last(s_n);
+    if (lane == 63) {
+        sh.red[wave][0] = s_is;
+        sh.red[wave][1] = s_js;
+        sh.red[wave][2] = s_n;
+    }
+#pragma unroll
+    for (int t = 0; t < kWinX * kWinY; t += 64 * W) sh.win[t + (int)threadIdx.x] = 0;
+    __syncthreads();
+    float m_is = 0.0f, m_js = 0.0f, total = 0.0f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        m_is += sh.red[w][0];
+        m_js += sh.red[w][1];
+        total += sh.red[w][2];
+    }
+    if (total == 0.0f) return;   // uniform
+    const int ox = uniform((int)(m_is / total)) - kWinX / 2, oy = uniform((int)(m_js / total)) - kWinY / 2;
+#pragma unroll
+    for (int b = 0; b < CY; ++b)
+#pragma unroll
+        for (int a = 0; a < CX; ++a) {
+            if (is[b][a] < 0) continue;
+            const unsigned wx = (unsigned)(is[b][a] - ox), wy = (unsigned)(js[b][a] - oy);
+            if (wx < (unsigned)kWinX && wy < (unsigned)kWinY)
+                atomicAdd(&sh.win[wy * kWinX + wx], 1);
+            else
+                atomicAdd(&p.counts[js[b][a] * p.NX + is[b][a]], 1);
+        }
+    __syncthreads();
+    // a wave per row of the window
+    constexpr int kAhead = kWinY / W < 8 ? kWinY / W : 8;
+    const int gx = ox + lane;
+    const bool in_map = gx >= 0 && gx < p.NX;
+#pragma unroll 1
+    for (int r0 = 0; r0 < kWinY / W; r0 += kAhead) {
+        int v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) v[u] = sh.win[((r0 + u) * W + wave) * kWinX + lane];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int gy = oy + (r0 + u) * W + wave;
+            if (v[u] && in_map && gy >= 0 && gy < p.NY) atomicAdd(&p.counts[gy * p.NX + gx], v[u]);
+        }
+    }
+    if (threadIdx.x == 0 && p.n_binned) atomicAdd(p.n_binned, (unsigned long long)total);   // at most 2048: exact
+}
+
+// One pass over a lattice too small to give every SIMD rays of its own: the W
+// waves of a workgroup hold the same tile, 8 x 8 lanes of CX x CY rays, and
+// each sums a W-th of the stars (contiguous runs).  The partial sums meet in
+// LDS, one component at a time; a ray's are added in run order after its macro
+// term, and each wave finishes a W-th of the rays.  Bound by VALU issue like
+// the one-pass kernel, whose tiles are 4 times as large for (8, 4) (8192
+// rays: 1000^2 rays are 128 workgroups).  100 stars, 1000^2 rays: 64 -> 31 us;
+// 3001 stars, 1201 x 777 rays: 1357 -> 618 us (4.5e12 ray-star terms a second).
+// The shorter runs round less: 2e-16 of beta (median over rays, 300 to 3000
+// stars, against 80-bit sums) where one run over all stars has 1e-15.
+template <int CX, int CY, int SHARE, int NS, int W>
+__global__ __launch_bounds__(64 * W, W <= 8 ? 2 : 4) void waves_fp64_kernel(ShootParams p) {
+    constexpr int R = CX * CY;                       // a lane's rays
+    constexpr int F = R > W ? R / W : 1;             // of which it finishes
+    constexpr int FX = F < CX ? F : CX, FY = F / FX;
+    static_assert(FX * FY == F && R % F == 0 && R / F <= W && CX % FX == 0, "rays of the epilogue");
+    __shared__ union {
+        double part[W][R][64];
+        WavesBin<W> bin;
+    } sh;
+    const int lane = threadIdx.x % 64, wave = uniform(threadIdx.x / 64);
+    const int lx = lane % 8, ly = lane / 8;
+    const int64_t tiles_x = uniform(p.tiles_x);
+    const int64_t tile_i = (blockIdx.x % tiles_x) * (8 * CX), tile_j = (blockIdx.x / tiles_x) * (8 * CY);
+    {
+        double tx[CX], ty[CY], ax[CY][CX], ay[CY][CX];
+#pragma unroll
+        for (int a = 0; a < CX; ++a) tx[a] = image_angle(p.x0, p.i0 + tile_i + lx + 8 * a, p.dx);
+#pragma unroll
+        for (int b = 0; b < CY; ++b) ty[b] = image_angle(p.y0, p.j0 + tile_j + ly + 8 * b, p.dy);
+#pragma unroll
+        for (int b = 0; b < CY; ++b)
+#pragma unroll
+            for (int a = 0; a < CX; ++a) ax[b][a] = ay[b][a] = 0.0;
+        const int64_t n = uniform(p.n_stars);
+        const int k0 = (int)(n * wave / W), k1 = (int)(n * (wave + 1) / W);
+        lane_star_sums<CX, CY, SHARE, NS, false>(p, const_stars(uniform_ptr(p.stars)), k0, k1, tx, ty, ax, ay);
+#pragma unroll
+        for (int r = 0; r < R; ++r) sh.part[wave][r][lane] = ax[r / CX][r % CX];
+        __syncthreads();
+        // read below: the wave's rays r0 ... r0 + F - 1, in the x component
+        // now, in y after the other half of the sums has taken its place
+        const bool mine = wave * F < R;
+        const int r0 = mine ? wave * F : 0;
+        const int64_t fi = tile_i + 8 * (r0 % CX), fj = tile_j + 8 * (r0 / CX);
+        double fx[FX], fy[FY], sx[FY][FX], sy[FY][FX];
+#pragma unroll
+        for (int a = 0; a < FX; ++a) fx[a] = image_angle(p.x0, p.i0 + fi + lx + 8 * a, p.dx);
+#pragma unroll
+        for (int b = 0; b < FY; ++b) fy[b] = image_angle(p.y0, p.j0 + fj + ly + 8 * b, p.dy);
+#pragma unroll
+        for (int b = 0; b < FY; ++b)
+#pragma unroll
+            for (int a = 0; a < FX; ++a) macro_term(p, fx[a], fy[b], sx[b][a], sy[b][a]);
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+#pragma unroll
+            for (int f = 0; f < F; ++f) sx[f / FX][f % FX] += sh.part[w][r0 + f][lane];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) sh.part[wave][r][lane] = ay[r / CX][r % CX];
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+#pragma unroll
+            for (int f = 0; f < F; ++f) sy[f / FX][f % FX] += sh.part[w][r0 + f][lane];
+        __syncthreads();   // sh.bin takes the place of sh.part
+        finish_waves<FX, FY, W>(p, sh.bin, mine, fx, fy, sx, sy, fi, fj, lane, wave);
+    }
+}
+
 // Persistent form: workgroups take items (runs of ray tiles of one set)
 // from a device queue until it is empty.  The item's set is staged in LDS;
 // the values the star loop needs are moved to scalar registers.  At least
@@ -454,6 +634,44 @@ hipError_t launch(const ShootParams &p, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Shapes of waves_fp64_kernel.
+#define RAYSH_FP64_WAVES(X) \
+    X(8, 4, 16, 1, 4)       \
+    X(4, 4, 16, 1, 8)       \
+    X(4, 2, 8, 1, 16)       \
+    X(2, 2, 4, 1, 16)
+
+// Time of the busiest compute unit, in instructions of a lane (64 lanes a
+// cycle), of a launch whose workgroups each take a tile of w x h rays and
+// `once` besides the star sum.  A ray and star take 6 instructions, a lane's
+// column and row one and two (shared by its rays), a reciprocal four with its
+// tree, and a mass per ray half of one.  A unit takes whole tiles, and the
+// last of them runs partly alone (0.15 of a tile: 2048^2 rays and 10000 stars
+// take 8.63 ms in 2 tiles a unit and 8.03 in 8, 4096^2 rays and 16384 stars
+// 52.7 in 8 and 51.8 in 32); a unit with one wave a SIMD for all its tiles
+// issues 0.8 times as fast.
+double busiest_unit(const ShootParams &p, const TileShape &t, int w, int h, int waves, double once, int n_cu) {
+    const int64_t tiles = ((p.nx + w - 1) / w) * ((p.ny + h - 1) / h);
+    const int64_t mine = (tiles + n_cu - 1) / n_cu;
+    const double v = 6.0 + 1.0 / t.cy + 2.0 / t.cx + 4.0 / t.share + (t.star_tile > 1 ? 0.5 : 0.0);
+    const double last = mine * waves >= 8 ? 0.15 : 0.25;
+    return ((double)mine + last) * (double)p.n_stars * w * h * v + (double)mine * once;
+}
+
+// A tile's epilogue, in the same unit: 16 us for 8192 rays, about 4 for each
+// shape of waves_fp64_kernel (1000^2 rays and 10 stars: 21 us in one such
+// tile a unit, 11.6 in two of 2048 rays, 41 in eight of 512).
+constexpr double kOncePerTile = 2.4e6, kOnceShared = 6.5e5;
+
+template <int CX, int CY, int SHARE, int NS, int W>
+hipError_t launch_waves(const ShootParams &p, hipStream_t s) {
+    ShootParams q = p;
+    q.tiles_x = (int32_t)((p.nx + 8 * CX - 1) / (8 * CX));
+    const int64_t blocks = (int64_t)q.tiles_x * ((p.ny + 8 * CY - 1) / (8 * CY));
+    hipLaunchKernelGGL((waves_fp64_kernel<CX, CY, SHARE, NS, W>), dim3((unsigned)blocks), dim3(64 * W), 0, s, q);
+    return hipGetLastError();
+}
+
 template <int CX, int CY, int SHARE, int NS>
 hipError_t launch_split(const ShootParams &p, int parts, double2 *partial, hipStream_t s) {
     ShootParams q = p;
@@ -523,6 +741,30 @@ hipError_t launch_shoot_fp64(const ShootParams &p, const TileShape &t, hipStream
     RAYSH_FP64_SHAPES(RAYSH_CASE)
 #undef RAYSH_CASE
     return hipErrorInvalidValue;
+}
+
+// One pass in the fastest form for the lattice: `t` (the shape for lattices
+// that fill the device many times over) or the waves of a workgroup sharing a
+// tile, whichever keeps the busiest compute unit busy least.  Measured (us, t
+// and the form chosen): 100 stars and 1000^2 rays 64 -> 31, 1000 and 500^2
+// 458 -> 62, 1000 and 250^2 457 -> 25, 3000 and 100^2 1343 -> 58, 10000 and
+// 2048^2 8630 -> 8030; 1000 and 8192^2 stay with t (12.70 ms against 12.91,
+// its epilogue being cheaper a ray).
+hipError_t launch_shoot_fp64_auto(const ShootParams &p, const TileShape &t, int n_cu, hipStream_t s) {
+    if (n_cu < 1) n_cu = 1;
+    double best = 0.99 * busiest_unit(p, t, tile_width(t), tile_height(t), kThreads / 64, kOncePerTile, n_cu);
+    hipError_t (*run)(const ShootParams &, hipStream_t) = nullptr;
+#define RAYSH_CASE(CX, CY, S, NS, W)                                                                     \
+    {                                                                                                    \
+        const double cost = busiest_unit(p, TileShape{CX, CY, S, NS}, 8 * CX, 8 * CY, W, kOnceShared, n_cu); \
+        if (cost < best) {                                                                               \
+            best = cost;                                                                                 \
+            run = launch_waves<CX, CY, S, NS, W>;                                                        \
+        }                                                                                                \
+    }
+    RAYSH_FP64_WAVES(RAYSH_CASE)
+#undef RAYSH_CASE
+    return run ? run(p, s) : launch_shoot_fp64(p, t, s);
 }
 
 hipError_t launch_split_fp64(const ShootParams &p, const TileShape &t, int parts, double2 *partial,
