@@ -195,7 +195,7 @@ int raysh_set_expansion_block(raysh_ctx *ctx, int block);
  * the cell's radius r_c).  A cell whose centre lies at least
  * (r_c + rho) / theta_open from a block's centre enters the block's local
  * expansion through it (a multipole-to-local translation: exact algebra
- * up to truncation at the same order and the same error bound per cell);
+ * up to truncation, at the same error bound per cell);
  * the stars of the other cells are tested one by one as without cells.
  * This is the cell expansion of distant stars that the tree codes of the
  * paper's Sec. 1 rest on.  The near stars are the same with or without

@@ -119,41 +119,72 @@ __device__ __forceinline__ void region_uniform(const ShootParams &p, int64_t i, 
     rho = uniform_f64(rho);
 }
 
+// Maximum of a non-negative float over the wave, uniform.
+__device__ __forceinline__ float wave_max(float v) {
+#define RAYSH_DPP_MAX(ctrl, rows) \
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, rows, 0xf, true)))
+    RAYSH_DPP_MAX(0x111, 0xf);   // row_shr 1, 2, 4, 8: lane 15 of each row of 16
+    RAYSH_DPP_MAX(0x112, 0xf);
+    RAYSH_DPP_MAX(0x114, 0xf);
+    RAYSH_DPP_MAX(0x118, 0xf);
+    RAYSH_DPP_MAX(0x142, 0xa);   // row_bcast 15 into rows 1 and 3
+    RAYSH_DPP_MAX(0x143, 0xc);   // row_bcast 31 into rows 2 and 3
+#undef RAYSH_DPP_MAX
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
+// The order at which a series in theta may stop: the smallest P with
+// theta^(P + 1) <= 2^-56, at most `most` (theta2 = theta^2, uniform).
+__device__ __forceinline__ int order_for(float theta2, int most) {
+    const float l = -__log2f(theta2);   // +inf for 0
+    const float P = 112.0f / l;
+    return uniform(P >= 0.0f && P < (float)most ? (int)P : most);   // theta >= 1 or NaN: all terms
+}
+
 // One pass over `count` entries split into four contiguous quarters, one per
 // wave.  fetch(e, k, x, y, m) gives entry e's star: its index k and record.
 // A star farther than sqrt(r_near2) from (cx, cy) adds m u (-u rho)^q to
 // the lane's coefficients; a nearer one is appended to its wave's out list,
 // so that the concatenated out lists keep the entries' order.  out_n counts
 // every near star, also beyond the capacity.
-template <class Fetch>
+// SORTED: the stars come by cell.  Their fetches are longer (one is under way
+// while the star before it is summed), and 64 of them lie close together, so
+// the series stops at the order that the nearest one needs.  (Without an order
+// the nearest of 64 needs most terms, and the tests and the registers, 222
+// for 132, cost more: 16384 stars, 8192^2 rays 113 -> 138 us.)
+template <bool SORTED, class Fetch>
 __device__ __forceinline__ void p2l_pass(int count, Fetch fetch, double cx, double cy, double rho, double r_near2,
                                          double2 (&acc)[kOrder + 1], int (*out_idx)[kNearPerWave], int *out_n) {
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     const int per_wave = (count + kWaves - 1) / kWaves;
-    const int w0 = wave * per_wave < count ? wave * per_wave : count;
-    const int w1 = w0 + per_wave < count ? w0 + per_wave : count;
+    const int w0 = uniform(wave * per_wave < count ? wave * per_wave : count);
+    const int w1 = uniform(w0 + per_wave < count ? w0 + per_wave : count);
     int found = 0;   // this wave's near stars so far (uniform in the wave)
+    int nk = 0;
+    double nx = 0.0, ny = 0.0, nm = 0.0;
+    if (SORTED && w0 + lane < w1) fetch(w0 + lane, nk, nx, ny, nm);
     for (int base = w0; base < w1; base += 64) {
-        const int e = base + lane;
-        bool near = false;
-        int k = 0;
-        if (e < w1) {
-            double sx, sy, sm;
-            fetch(e, k, sx, sy, sm);
-            const double dx = cx - sx, dy = cy - sy;
-            const double d2 = dx * dx + dy * dy;
-            near = d2 <= r_near2;
-            if (!near) {
-                const double inv = 1.0 / d2;
-                const double2 u = make_double2(dx * inv, -dy * inv);        // 1 / (c - z_k)
-                const double2 mu = make_double2(-u.x * rho, -u.y * rho);    // -u rho
-                double2 t = make_double2(sm * u.x, sm * u.y);               // m u
+        const bool valid = base + lane < w1;
+        if (!SORTED && valid) fetch(base + lane, nk, nx, ny, nm);
+        const int k = nk;
+        const double sm = nm;
+        const double dx = cx - nx, dy = cy - ny;
+        const double d2 = dx * dx + dy * dy;
+        if (SORTED && base + 64 + lane < w1) fetch(base + 64 + lane, nk, nx, ny, nm);
+        const bool near = valid && d2 <= r_near2;
+        const double inv = 1.0 / d2;
+        int order = kOrder;
+        if (SORTED) order = order_for(wave_max(valid && !near ? (float)(rho * rho * inv) : 0.0f), kOrder);
+        if (valid && !near) {
+            const double2 u = make_double2(dx * inv, -dy * inv);        // 1 / (c - z_k)
+            const double2 mu = make_double2(-u.x * rho, -u.y * rho);    // -u rho
+            double2 t = make_double2(sm * u.x, sm * u.y);               // m u
 #pragma unroll
-                for (int q = 0; q <= kOrder; ++q) {
-                    acc[q].x += t.x;
-                    acc[q].y += t.y;
-                    if (q < kOrder) t = cmul(t, mu);
-                }
+            for (int q = 0; q <= kOrder; ++q) {
+                if (SORTED && q % 4 == 1 && q > order) break;
+                acc[q].x += t.x;
+                acc[q].y += t.y;
+                if (q < kOrder) t = cmul(t, mu);
             }
         }
         const unsigned long long ball = __ballot(near);
@@ -186,20 +217,34 @@ __constant__ CellBinomialTable kCellBinomial = make_cell_binomials();
 // translated to the local expansion of a region of centre C and radius
 // rho, added to acc.  With D = C - z_c, w = 1/D and g = -rho w,
 //   sum_k m_k / (C + rho s - z_k) = w sum_j M_j (r_c w)^j sum_q C(j + q, q) g^q s^q,
-// which converges for (r_c + rho) < |D| and, truncated at kOrder in j and
-// q, leaves at most theta^(kOrder+1) / (1 - theta) of the cell's field with
-// theta = (r_c + rho) / |D|, the bound of the per-star expansion.
-__device__ __forceinline__ void m2l_cell(const double2 *M, double dx, double dy, double rc, double rho,
+// which converges for (r_c + rho) < |D|.  The terms of total degree n = j + q
+// add up to at most theta^n of the cell's field, theta = (r_c + rho) / |D|,
+// those of one j to (a / (1 - g))^j and those of one q to (g / (1 - a))^q, with
+// a = r_c / |D| and g = rho / |D| here; the sums stop where each bound is
+// below 2^-56 for the wave's nearest cells (and at kOrder in j and in q), so
+// what is dropped stays below theta^(kOrder+1) / (1 - theta), the bound of the
+// per-star expansion.  A cell 14 r_c away takes 14 terms where all 25 x 25
+// took 625.
+__device__ __forceinline__ void m2l_cell(const double2 *M, double dx, double dy, double rc, double rho, bool active,
                                          double2 (&acc)[kOrder + 1]) {
     const double inv = 1.0 / (dx * dx + dy * dy);
+    const float fa = wave_max(active ? (float)__builtin_sqrt(rc * rc * inv) : 0.0f);
+    const float fg = wave_max(active ? (float)__builtin_sqrt(rho * rho * inv) : 0.0f);
+    const auto sq = [](float x) { return x * x; };
+    const int degree = order_for(sq(fa + fg), 2 * kOrder);
+    const int most_j = min(order_for(sq(fa / (1.0f - fg)), kOrder), degree);
+    const int most_q = order_for(sq(fg / (1.0f - fa)), kOrder);
+    if (!active) return;
     const double2 w = make_double2(dx * inv, -dy * inv);
     const double2 g = make_double2(-rho * w.x, -rho * w.y);
     const double2 a = make_double2(rc * w.x, rc * w.y);
     double2 ap = w;   // w (r_c w)^j
-    for (int j = 0; j <= kOrder; ++j) {   // uniform trip count
+    for (int j = 0; j <= most_j; ++j) {   // uniform trip count
         double2 t = cmul(M[j], ap);
+        const int last = min(most_q, degree - j);   // uniform
 #pragma unroll
         for (int q = 0; q <= kOrder; ++q) {
+            if (q % 3 == 1 && q > last) break;
             const double b = kCellBinomial.c[j][q];
             acc[q].x = __builtin_fma(b, t.x, acc[q].x);
             acc[q].y = __builtin_fma(b, t.y, acc[q].y);
@@ -345,28 +390,39 @@ __device__ __forceinline__ void block_pass_cells(const StarCells &cells, double 
     __syncthreads();
     // every non-empty cell outside the bands, through its multipole expansion
     const int n_cells = ncx * ncy;
-    for (int c = threadIdx.x; c < n_cells; c += kThreads) {
-        const int i = c % ncx, jj = c / ncx;
-        if (i >= ex.row_lo[jj] && i <= ex.row_hi[jj]) continue;
-        if (cells.start[c + 1] == cells.start[c]) continue;
+    for (int base = 0; base < n_cells; base += kThreads) {   // uniform
+        const int c = base + threadIdx.x;
+        bool far = false;
+        int i = 0, jj = 0;
+        if (c < n_cells) {
+            i = c % ncx;
+            jj = c / ncx;
+            far = (i < ex.row_lo[jj] || i > ex.row_hi[jj]) && cells.start[c + 1] != cells.start[c];
+        }
         const double dx = bcx - (gx0 + ((double)i + 0.5) * h);
         const double dy = bcy - (gy0 + ((double)jj + 0.5) * h);
-        m2l_cell(cells.mult + (size_t)c * (kOrder + 1), dx, dy, rc, brho, acc);
+        m2l_cell(cells.mult + (size_t)(far ? c : 0) * (kOrder + 1), dx, dy, rc, brho, far, acc);
     }
     // the bands' stars, one by one: entry e is in the last row whose prefix
     // is at most e (rows before it hold fewer stars, empty rows share their
-    // successor's prefix)
+    // successor's prefix); a lane's entries ascend, and so do their rows
     const Star *sorted = cells.sorted;
-    p2l_pass(
+    int row = -1, row_end = 0, shift = 0;   // the row of the lane's last entry, the first entry past it
+    p2l_pass<true>(
         uniform(total),
         [&](int e, int &k, double &x, double &y, double &m) {
-            int lo = 0, hi = ncy - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) / 2;
-                if (ex.row_pref[mid] <= e) lo = mid;
-                else hi = mid - 1;
+            if (e >= row_end) {
+                int lo = row < 0 ? 0 : row, hi = ncy - 1;
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) / 2;
+                    if (ex.row_pref[mid] <= e) lo = mid;
+                    else hi = mid - 1;
+                }
+                row = lo;
+                row_end = lo + 1 < ncy ? ex.row_pref[lo + 1] : 0x7fffffff;
+                shift = ex.row_first[lo] - ex.row_pref[lo];
             }
-            const Star st = sorted[ex.row_first[lo] + (e - ex.row_pref[lo])];
+            const Star st = sorted[shift + e];
             x = st.x;
             y = st.y;
             m = st.m;
@@ -379,7 +435,10 @@ __device__ __forceinline__ void block_pass_cells(const StarCells &cells, double 
 // the stars far from the block enter its local expansion A (through star
 // cells when CELLS), the near ones go to its lists; both are written to
 // far[blockIdx.x] for the tile kernel.  Two workgroups per compute unit: the
-// cells' translations need the registers.
+// cells' translations need the registers.  262144 stars, 2048^2 rays, one
+// workgroup a unit: 104 -> 65 us with the series cut at the order that each
+// wave's nearest cell or star needs, and the next star fetched ahead; bound by
+// VALU issue with one wave a SIMD, and latency.
 template <bool CELLS>
 __global__ __launch_bounds__(kThreads, 2) void expansion_block_kernel(ShootParams p, StarCells cells,
                                                                       double theta_open, int blocks_x,
@@ -401,7 +460,7 @@ __global__ __launch_bounds__(kThreads, 2) void expansion_block_kernel(ShootParam
     if constexpr (CELLS) {
         block_pass_cells(cells, bcx, bcy, brho, inv_theta, r_near2, acc, ex);
     } else {
-        p2l_pass(
+        p2l_pass<false>(
             n,
             [&](int e, int &k, double &x, double &y, double &m) {
                 k = e;
@@ -1108,9 +1167,10 @@ void free_star_cells(StarCellStore &c) {
 // The cell side balances a block's two costs: the stars of its open cells,
 // tested one by one (their number grows as side^2), against the
 // translations of the other cells (whose number falls as 1/side^2, each
-// about 26 times the work of one star's expansion).  Their sum is least
-// near side = sqrt(area / sqrt(N*)) for theta_open = 0.25; the grid is then
-// coarsened until it fits the workgroup's tables.
+// about 6 times the work of one star's expansion).  Their sum is least
+// near side^2 = area / (2 sqrt(N*)) for theta_open = 0.25 (262144 stars,
+// 4096^2 rays: 446, 422, 459 and 488 us for 1, 2, 4 and 8 in place of the 2);
+// the grid is then coarsened until it fits the workgroup's tables.
 hipError_t build_star_cells(const Star *d_stars, int64_t n_stars, hipStream_t s, StarCellStore &out) {
     free_star_cells(out);
     if (n_stars < 2 || n_stars > kCellMaxStars) return hipSuccess;   // no cells
@@ -1128,7 +1188,7 @@ hipError_t build_star_cells(const Star *d_stars, int64_t n_stars, hipStream_t s,
     const double w = x1 - x0, hgt = y1 - y0, big = std::max(w, hgt);
     if (!(big > 0.0)) return hipSuccess;   // every star at one point: no cells
     const double area = std::max(w * hgt, 1e-6 * big * big);
-    double side = std::sqrt(area / std::sqrt((double)n_stars));
+    double side = std::sqrt(area / (2.0 * std::sqrt((double)n_stars)));
     int ncx = 0, ncy = 0;
     for (;;) {
         ncx = (int)std::min(std::floor(w / side) + 1.0, 1e9);

@@ -133,3 +133,20 @@ def test_pixel_step(torch, pix):
     with R.Context(lens) as ctx:
         for rays in ((-1.025, -1.025, 0.05, 0.05, 82, 82, 0, 0), (-1.0003, -0.9, 0.0031, 0.0083, 650, 220, 0, 0)):
             _check(torch, ctx, lens, rays, pix)
+
+
+@pytest.mark.parametrize("spread", [1.0, 30.0])
+@pytest.mark.parametrize("block", [1, 4])
+@pytest.mark.parametrize("theta", [0.3, 0.25, 0.05])
+def test_series_cut_by_distance(torch, block, theta, spread):
+    """Star cells and their stars at distances from the opening radius to a
+    hundred block radii: series of few to all terms, in the same waves."""
+    rng = np.random.default_rng(int(100 * theta) + block)
+    n = 4000
+    r, phi = 0.3 * (spread * 400) ** rng.random(n), 2 * np.pi * rng.random(n)   # equally many per octave
+    lens = (0.1, 0.15, -0.05, r * np.cos(phi), r * np.sin(phi), rng.uniform(1e-3, 2e-3, n))
+    with R.Context(lens) as ctx:
+        ctx.set_expansion(theta)
+        ctx.set_expansion_block(block)
+        ctx.set_expansion_cells("always")
+        _check(torch, ctx, lens, (-0.8, -0.7, 0.008, 0.007, 200, 201, 0, 0), (-0.9, -0.8, 0.03, 0.02, 60, 81))
