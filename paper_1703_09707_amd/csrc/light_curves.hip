@@ -288,7 +288,11 @@ __global__ __launch_bounds__(kLcThreads, 8) void light_curve_track_kernel(
     int64_t n_tracks, int64_t n_chunks, int chunks_per_track, int n_samples, double inv_n1,
     double *__restrict__ out) {
 #pragma clang fp contract(off)
-    const int64_t chunk = wave_uniform((int64_t)blockIdx.x * (kLcThreads / 64) + threadIdx.x / 64);
+    // Workgroups go to the 8 XCDs in turn; each XCD takes a contiguous eighth
+    // of them, so that tracks next to each other in the order share an L2.
+    const unsigned eighth = gridDim.x / 8;   // whole rounds; the rest keep their place
+    const unsigned block = blockIdx.x < 8 * eighth ? blockIdx.x % 8 * eighth + blockIdx.x / 8 : blockIdx.x;
+    const int64_t chunk = wave_uniform((int64_t)block * (kLcThreads / 64) + threadIdx.x / 64);
     if (chunk >= n_chunks) return;   // uniform in the wave
     const int64_t tp = chunk / chunks_per_track;
     const int k0 = (int)(chunk - tp * chunks_per_track) * kWaveChunk;
@@ -352,7 +356,11 @@ __global__ __launch_bounds__(kLcThreads, 8) void light_curve_track_kernel(
 // --- track order: a counting sort of the tracks by the cell holding their
 // midpoint, cells of kCellPx x kCellPx pixels (larger for maps of more than
 // 2048 cells a side) numbered in Z (Morton) order, so that tracks that run
-// together on the GPU read neighbouring parts of the map.
+// together on the GPU read neighbouring parts of the map.  Where cells hold
+// kDirections tracks or more on average, each cell's are sorted again by
+// direction: tracks side by side then read the same rows all along, not only
+// near their midpoints (2^20 tracks of 250 samples, 205 of 1024 pixels long:
+// curves 858 -> 689 us, 671 with the XCDs' eighths in the kernel above).
 constexpr int kCellPx = 16;
 constexpr int kMaxCellsPerSide = 2048;
 constexpr int kScanThreads = 1024;
@@ -362,6 +370,15 @@ constexpr int kScanThreads = 1024;
 // served one after another (with 4096 cells, 32 counters a line took 256 x
 // 32 atomics each).  Beyond 32768 cells the tracks spread over enough lines.
 inline int counter_stride(int64_t n_keys) { return n_keys <= 32768 ? 32 : 1; }
+
+// Directions take the place of that spacing: as many words, 16 counters of a
+// cell 2 words apart, so that a line gets the atomics of one cell either way.
+constexpr uint32_t kDirections = 16;
+constexpr int kDirectionStride = 2;
+
+inline bool sort_directions(int64_t n_keys, int64_t n_tracks) {
+    return counter_stride(n_keys) == kDirections * kDirectionStride && n_tracks >= n_keys * kDirections;
+}
 
 struct CellGrid {
     double x0, y0, ipx, ipy;   // map origin and inverse pixel size
@@ -400,12 +417,20 @@ __device__ __forceinline__ uint32_t morton(uint32_t x, uint32_t y) {
 
 // The counting and the scattering pass must agree on every key: the same
 // operations, none contracted.
+template <bool DIRECTIONS>
 __device__ __forceinline__ uint32_t track_key(const CellGrid &c, double xa, double ya, double xb, double yb) {
 #pragma clang fp contract(off)
     const double mx = 0.5 * (xa + xb), my = 0.5 * (ya + yb);
     const int cx = cell_of(((mx - c.x0) * c.ipx) / (double)c.cell_px, c.cells_x);
     const int cy = cell_of(((my - c.y0) * c.ipy) / (double)c.cell_px, c.cells_y);
-    return morton((uint32_t)cx, (uint32_t)cy);
+    const uint32_t cell = morton((uint32_t)cx, (uint32_t)cy);
+    if (!DIRECTIONS) return cell;
+    // the direction without its sense, as the place along |x| + |y| = 1 from
+    // (1, 0) to (-1, 0) (any monotone measure of the angle will do)
+    const double dx = (xb - xa) * c.ipx, dy = (yb - ya) * c.ipy;
+    const double along = (dy < 0.0 ? -dx : dx) / (fabs(dx) + fabs(dy));
+    const double d = (1.0 - along) * (0.5 * kDirections);   // in [0, kDirections], or NaN: direction 0
+    return cell * kDirections + (d >= 0.0 ? min((uint32_t)d, kDirections - 1u) : 0u);
 }
 
 __global__ void zero_u32_kernel(uint32_t *p, int64_t n) {
@@ -413,12 +438,13 @@ __global__ void zero_u32_kernel(uint32_t *p, int64_t n) {
     if (i < n) p[i] = 0;
 }
 
+template <bool DIRECTIONS>
 __global__ __launch_bounds__(kLcThreads) void track_count_kernel(CellGrid c, const double *xa, const double *ya,
                                                                  const double *xb, const double *yb,
                                                                  int64_t n_tracks, int stride, uint32_t *counts) {
     const int64_t t = (int64_t)blockIdx.x * kLcThreads + threadIdx.x;
     if (t >= n_tracks) return;
-    atomicAdd(&counts[(int64_t)track_key(c, xa[t], ya[t], xb[t], yb[t]) * stride], 1u);
+    atomicAdd(&counts[(int64_t)track_key<DIRECTIONS>(c, xa[t], ya[t], xb[t], yb[t]) * stride], 1u);
 }
 
 // Exclusive prefix sum of counts[0], counts[stride], ... (n values) in place
@@ -450,6 +476,65 @@ __global__ __launch_bounds__(kScanThreads) void track_scan_kernel(uint32_t *coun
     }
 }
 
+// The same for the counts of cells' directions, up to 2^19 of them, in two
+// steps: the sum of each workgroup's counts, then every count's prefix.  The
+// counts are in the even words; workgroup b's sum goes to the odd word 2 b + 1.
+constexpr int kScanCounts = 2048;   // of a workgroup of 256 threads, 8 each
+
+__device__ __forceinline__ uint32_t load_counts(const uint32_t *counts, int64_t first, int64_t n, uint32_t (&v)[8]) {
+    uint32_t sum = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        v[u] = first + u < n ? counts[(first + u) * kDirectionStride] : 0u;
+        sum += v[u];
+    }
+    return sum;
+}
+
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+__global__ __launch_bounds__(256) void track_block_sums_kernel(uint32_t *counts, int64_t n) {
+    __shared__ uint32_t wave_tot[4];
+    uint32_t v[8];
+    const uint32_t sum = wave_sum_u32(load_counts(counts, (int64_t)blockIdx.x * kScanCounts + threadIdx.x * 8, n, v));
+    if (threadIdx.x % 64 == 0) wave_tot[threadIdx.x / 64] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        counts[blockIdx.x * kDirectionStride + 1] = wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
+}
+
+__global__ __launch_bounds__(256) void track_prefix_kernel(uint32_t *counts, int64_t n) {
+    __shared__ uint32_t wave_tot[4], wave_before[4];
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const int64_t first = (int64_t)blockIdx.x * kScanCounts + threadIdx.x * 8;
+    uint32_t v[8];
+    const uint32_t sum = load_counts(counts, first, n, v);
+    uint32_t before = 0;   // the workgroups before this one
+    for (unsigned b = threadIdx.x; b < blockIdx.x; b += 256) before += counts[b * kDirectionStride + 1];
+    before = wave_sum_u32(before);
+    uint32_t incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t up = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += up;
+    }
+    if (lane == 63) wave_tot[wave] = incl;
+    if (lane == 0) wave_before[wave] = before;
+    __syncthreads();
+    uint32_t run = wave_before[0] + wave_before[1] + wave_before[2] + wave_before[3] + incl - sum;
+    for (int w = 0; w < wave; ++w) run += wave_tot[w];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        if (first + u < n) counts[(first + u) * kDirectionStride] = run;
+        run += v[u];
+    }
+}
+
+template <bool DIRECTIONS>
 __global__ __launch_bounds__(kLcThreads) void track_scatter_kernel(CellGrid c, const double *xa, const double *ya,
                                                                    const double *xb, const double *yb,
                                                                    int64_t n_tracks, int stride, uint32_t *offsets,
@@ -457,7 +542,7 @@ __global__ __launch_bounds__(kLcThreads) void track_scatter_kernel(CellGrid c, c
     const int64_t t = (int64_t)blockIdx.x * kLcThreads + threadIdx.x;
     if (t >= n_tracks) return;
     const double ax = xa[t], ay = ya[t], bx = xb[t], by = yb[t];
-    const uint32_t pos = atomicAdd(&offsets[(int64_t)track_key(c, ax, ay, bx, by) * stride], 1u);
+    const uint32_t pos = atomicAdd(&offsets[(int64_t)track_key<DIRECTIONS>(c, ax, ay, bx, by) * stride], 1u);
     order[pos] = (int32_t)t;   // pos < n_tracks: the offsets partition [0, n_tracks)
     if (sorted) {
         sorted[pos] = ax;
@@ -625,11 +710,22 @@ extern "C" int raysh_track_order(const raysh_pixels *grid, int64_t n_tracks, con
     uint32_t *counts = (uint32_t *)workspace;
     const unsigned tb_blocks = (unsigned)((n_tracks + kLcThreads - 1) / kLcThreads);
     hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)((n_words + 255) / 256)), dim3(256), 0, s, counts, n_words);
-    hipLaunchKernelGGL(track_count_kernel, dim3(tb_blocks), dim3(kLcThreads), 0, s, c, xa, ya, xb, yb, n_tracks,
-                       stride, counts);
-    hipLaunchKernelGGL(track_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, counts, n_keys, stride);
-    hipLaunchKernelGGL(track_scatter_kernel, dim3(tb_blocks), dim3(kLcThreads), 0, s, c, xa, ya, xb, yb, n_tracks,
-                       stride, counts, order, sorted);
+    if (sort_directions(n_keys, n_tracks)) {
+        const int64_t n_counts = n_keys * kDirections;
+        const dim3 scan_blocks((unsigned)((n_counts + kScanCounts - 1) / kScanCounts));
+        hipLaunchKernelGGL(track_count_kernel<true>, dim3(tb_blocks), dim3(kLcThreads), 0, s, c, xa, ya, xb, yb,
+                           n_tracks, kDirectionStride, counts);
+        hipLaunchKernelGGL(track_block_sums_kernel, scan_blocks, dim3(256), 0, s, counts, n_counts);
+        hipLaunchKernelGGL(track_prefix_kernel, scan_blocks, dim3(256), 0, s, counts, n_counts);
+        hipLaunchKernelGGL(track_scatter_kernel<true>, dim3(tb_blocks), dim3(kLcThreads), 0, s, c, xa, ya, xb, yb,
+                           n_tracks, kDirectionStride, counts, order, sorted);
+    } else {
+        hipLaunchKernelGGL(track_count_kernel<false>, dim3(tb_blocks), dim3(kLcThreads), 0, s, c, xa, ya, xb, yb,
+                           n_tracks, stride, counts);
+        hipLaunchKernelGGL(track_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, counts, n_keys, stride);
+        hipLaunchKernelGGL(track_scatter_kernel<false>, dim3(tb_blocks), dim3(kLcThreads), 0, s, c, xa, ya, xb, yb,
+                           n_tracks, stride, counts, order, sorted);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "raysh_track_order");
     return set_ok();
