@@ -239,12 +239,15 @@ __device__ __forceinline__ void m2l_cell(const double2 *M, double dx, double dy,
     const double2 g = make_double2(-rho * w.x, -rho * w.y);
     const double2 a = make_double2(rc * w.x, rc * w.y);
     double2 ap = w;   // w (r_c w)^j
+    double2 m = M[0], m1 = M[min(1, most_j)];
     for (int j = 0; j <= most_j; ++j) {   // uniform trip count
-        double2 t = cmul(M[j], ap);
+        double2 t = cmul(m, ap);
+        m = m1;
+        m1 = M[min(j + 2, most_j)];   // two terms ahead: a lane's loads miss its L1
         const int last = min(most_q, degree - j);   // uniform
 #pragma unroll
         for (int q = 0; q <= kOrder; ++q) {
-            if (q % 3 == 1 && q > last) break;
+            if (q % 2 == 1 && q > last) break;
             const double b = kCellBinomial.c[j][q];
             acc[q].x = __builtin_fma(b, t.x, acc[q].x);
             acc[q].y = __builtin_fma(b, t.y, acc[q].y);
@@ -436,9 +439,10 @@ __device__ __forceinline__ void block_pass_cells(const StarCells &cells, double 
 // cells when CELLS), the near ones go to its lists; both are written to
 // far[blockIdx.x] for the tile kernel.  Two workgroups per compute unit: the
 // cells' translations need the registers.  262144 stars, 2048^2 rays, one
-// workgroup a unit: 104 -> 65 us with the series cut at the order that each
-// wave's nearest cell or star needs, and the next star fetched ahead; bound by
-// VALU issue with one wave a SIMD, and latency.
+// workgroup a unit: 104 -> 55 us with the series cut at the order that each
+// wave's nearest cell or star needs, and the next star and multipoles fetched
+// ahead (the multipoles' part: 117 -> 110 us a map); bound by VALU issue with
+// one wave a SIMD, and latency.
 template <bool CELLS>
 __global__ __launch_bounds__(kThreads, 2) void expansion_block_kernel(ShootParams p, StarCells cells,
                                                                       double theta_open, int blocks_x,
