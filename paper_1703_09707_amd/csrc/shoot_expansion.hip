@@ -584,9 +584,15 @@ __device__ __forceinline__ double image_angle_at(double origin, double base, int
 constexpr int kCols = 2;
 constexpr int kRows = kPatchRays / 64;
 
-// Star (sx, sy, sm) added to a lane's rays, one reciprocal for all eight (a
-// product tree with the mass at its root, as in the one-pass kernel; a ray
-// on the star turns all eight NaN, see expansion_tile_kernel).
+// Star (sx, sy, sm) added to a lane's rays.  Each ray's reciprocal is its own
+// (the hardware's and one Newton step).  One for all eight from a product
+// tree takes 2 instructions a ray and star less, but its six roundings more
+// made the largest error of fields with few near stars up to four times as
+// large (11861 stars, 1498 x 4096 rays, 3000 of them against 80-bit sums:
+// 1.1e-14 for 3.1e-15; RMS 6.5e-16 for 5.9e-16), and a ray's value depend on
+// the rays beside it.  With the tree and without: 16384 stars, 8192^2 rays
+// 463 and 478 us; 5000 stars, 2000^2 rays 111 and 122; 60000 stars, 3000^2
+// rays, about 300 near stars a tile, 729 and 867.
 __device__ __forceinline__ void near_star(double sx, double sy, double sm, const double (&tx)[kCols],
                                           const double (&ty)[kRows], double (&ax)[kCols][kRows],
                                           double (&ay)[kCols][kRows]) {
@@ -596,21 +602,19 @@ __device__ __forceinline__ void near_star(double sx, double sy, double sm, const
         ey[k] = ty[k] - sy;
         ey2[k] = ey[k] * ey[k];
     }
-    double ex[kCols], r2[kCols * kRows], w[kCols * kRows];
 #pragma unroll
     for (int c = 0; c < kCols; ++c) {
-        ex[c] = tx[c] - sx;
-#pragma unroll
-        for (int k = 0; k < kRows; ++k) r2[c * kRows + k] = __builtin_fma(ex[c], ex[c], ey2[k]);
-    }
-    scaled_reciprocals<kCols * kRows>(r2, sm, w);
-#pragma unroll
-    for (int c = 0; c < kCols; ++c)
+        const double ex = tx[c] - sx;
 #pragma unroll
         for (int k = 0; k < kRows; ++k) {
-            ax[c][k] = __builtin_fma(w[c * kRows + k], ex[c], ax[c][k]);
-            ay[c][k] = __builtin_fma(w[c * kRows + k], ey[k], ay[c][k]);
+            const double r2 = __builtin_fma(ex, ex, ey2[k]);
+            double y = __builtin_amdgcn_rcp(r2);
+            y = __builtin_fma(y, __builtin_fma(-r2, y, 1.0), y);
+            const double w = sm * y;
+            ax[c][k] = __builtin_fma(w, ex, ax[c][k]);
+            ay[c][k] = __builtin_fma(w, ey[k], ay[c][k]);
         }
+    }
 }
 
 // The stars a tile sums directly, one after the other, uniform in the wave:
@@ -679,10 +683,10 @@ __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, con
 //      word (a tile has 4096 rays); two windows take turns, so that a tile
 //      needs one barrier, after which its window is merged into the map while
 //      the next tile fills the other.
-// Bound by VALU issue: about 170 instructions a ray (52 Horner, 8.5 per near
+// Bound by VALU issue: about 175 instructions a ray (52 Horner, 10.5 per near
 // star, 36 pixel and count, 15 for the first two phases), where 16 rays a lane
-// at order 24, each star's reciprocal a ray's own, took 273: 16384 stars and
-// 8192^2 rays 650 -> 405 us; the share of the chip's FP64 issue rate is alike.
+// at order 24 took 273: 16384 stars and 8192^2 rays 650 -> 420 us; the share
+// of the chip's FP64 issue rate is alike.
 // Three workgroups a compute unit: at four the registers spill.
 // MAP: counts only, with pixel_coordinate's form of the division (the usual
 // call); otherwise also the per-ray outputs, and the division where needed.
