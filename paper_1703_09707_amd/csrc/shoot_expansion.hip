@@ -64,7 +64,7 @@ constexpr int kPatchRays = 256;       // 16 x 16 / 2^k by 16 * 2^k
 constexpr int kPatchSide = 4;         // patches along a tile's sides
 constexpr int kPatches = kPatchSide * kPatchSide;
 constexpr int kMaxSkew = 2;           // |k|
-constexpr int kPatchOrder = 13;       // Taylor terms of a patch's polynomial (see expansion_tile_kernel)
+constexpr int kPatchOrder = 14;       // Taylor terms of a patch's polynomial (see expansion_tile_kernel)
 constexpr int kTileNear = 256;        // near-star list capacity of a tile
 constexpr int kCellMaxRows = kThreads;   // star-cell grid rows and columns: one thread per row
 constexpr int kCellMaxCells = 4096;
@@ -673,9 +673,11 @@ __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, con
 //      across, so its terms fall four times as fast: a star farther than
 //      rho / theta from the tile's centre is at least (1 / theta - 0.77) rho
 //      from the patch's, whose radius is 0.239 rho, and what is dropped is below
-//      (0.239 / (1 / theta - 0.77))^14 / (1 - 0.08) of its term: 1.4e-16
-//      for theta = 0.25 and 4e-15 for 0.3, under the bounds of the tile's own
-//      truncation (1.5e-15, 1.6e-13).  13 instead of 24 multiply-adds a ray.
+//      (0.239 / (1 / theta - 0.77))^15 / (1 - 0.08) of its term: 1.1e-17
+//      for theta = 0.25 and 3.8e-16 for 0.3, at or under the rounding of the
+//      term.  One order less dropped 1.4e-16 and 4e-15: ten times the rounding
+//      at 0.3 (the order takes 8 us of the 486 of 16384 stars, 8192^2 rays).
+//      14 instead of 24 multiply-adds a ray.
 //   3. Tile by tile, each wave evaluates four patches, four rays a lane: the
 //      polynomial by Horner, the near stars directly, the pixel, the count.
 //      Rays are counted as they come, in an LDS window around the pixel that
@@ -683,7 +685,7 @@ __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, con
 //      word (a tile has 4096 rays); two windows take turns, so that a tile
 //      needs one barrier, after which its window is merged into the map while
 //      the next tile fills the other.
-// Bound by VALU issue: about 175 instructions a ray (52 Horner, 10.5 per near
+// Bound by VALU issue: about 180 instructions a ray (56 Horner, 10.5 per near
 // star, 36 pixel and count, 15 for the first two phases), where 16 rays a lane
 // at order 24 took 273: 16384 stars and 8192^2 rays 650 -> 420 us; the share
 // of the chip's FP64 issue rate is alike.

@@ -38,3 +38,33 @@ def test_near_stars_do_not_depend_on_the_rays_beside(torch, block, n_stars):
         for (i0, j0), part in at.items():
             for w, p in zip(whole, part):
                 np.testing.assert_array_equal(w[j0:, i0:], p, err_msg=f"block {block} from ray ({i0}, {j0})")
+
+
+@pytest.mark.parametrize("block", [1, 4])
+@pytest.mark.parametrize("theta", [0.3, 0.25])
+def test_patches_keep_the_tile_polynomial(torch, block, theta):
+    """One star just outside a tile's opening radius, where its series falls
+    slowest, against the tile's order-24 polynomial in 80-bit arithmetic.
+    Tolerance: what a patch of order 14 may drop (3.8e-16 of the star's term at
+    theta 0.3, 1.1e-17 at 0.25) and six roundings of 2^-53 for the coefficient,
+    the re-centring and the evaluation."""
+    tol = {0.3: 3.8e-16, 0.25: 1.1e-17}[theta] + 6 * 2.0 ** -53
+    L = np.longdouble
+    d, n = 1.0 / 64, 64
+    rho = 0.5 * (n - 1) * d * np.sqrt(2.0)
+    t = ((np.arange(n) + 0.5) * d - 0.5 * n * d).astype(L)
+    z = t[None, :] + 1j * t[:, None]
+    for k in range(24):
+        phi, r = 2 * np.pi * (k + 0.5) / 24, rho / theta * (1 + 1e-9)
+        zx, zy, m = r * np.cos(phi), r * np.sin(phi), 2.0 ** 30
+        with R.Context((0.0, 0.0, 0.0, [zx], [zy], [m])) as ctx:
+            ctx.set_expansion(theta)
+            ctx.set_expansion_block(block)
+            gx, gy, _ = (a.cpu().numpy() for a in ctx.shoot((-32 * d, -32 * d, d, d, n, n, 0, 0), "fp64_expansion", PIX))
+        zk = L(zx) + 1j * L(zy)
+        series = np.ones_like(z)
+        for _ in range(24):
+            series = 1 + (z / zk) * series
+        f = -L(m) / zk * series   # m / (z - zk) up to order 24
+        err = np.hypot((gx - (z.real - f.real)).astype(float), (gy - (z.imag + f.imag)).astype(float))
+        assert np.all(err <= tol * (L(m) / abs(z - zk)).astype(float)), (k, float(err.max()))
