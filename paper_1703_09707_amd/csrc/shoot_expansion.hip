@@ -56,6 +56,7 @@ namespace {
 constexpr int kOrder = 24;            // Taylor terms B_0 .. B_kOrder
 constexpr int kWaves = kThreads / 64;
 constexpr int kNearPerWave = 512;     // near-star list capacity of each wave
+constexpr int kBlockNear = kWaves * kNearPerWave;   // near stars of a block whose lists hold
 // A tile is 4096 rays, 64 x 64 for a lattice of square cells.  For others it
 // is 64 / 2^k by 64 * 2^k (expansion_tiles), so that its sides come out as equal as
 // they can: near lists, and with them the stars summed directly, grow as the
@@ -65,7 +66,7 @@ constexpr int kPatchSide = 4;         // patches along a tile's sides
 constexpr int kPatches = kPatchSide * kPatchSide;
 constexpr int kMaxSkew = 2;           // |k|
 constexpr int kPatchOrder = 14;       // Taylor terms of a patch's polynomial (see expansion_tile_kernel)
-constexpr int kTileNear = 256;        // near-star list capacity of a tile
+constexpr int kTileNear = 256;        // near stars a tile keeps as a list of its own
 constexpr int kCellMaxRows = kThreads;   // star-cell grid rows and columns: one thread per row
 constexpr int kCellMaxCells = 4096;
 constexpr int64_t kCellMaxStars = int64_t(1) << 26;   // the host keeps two copies while building
@@ -566,7 +567,9 @@ struct TileShared {
     double patch_inv[kTilesPerGroup * kPatches];         // 1 / radius
     unsigned win[2][kWinWords];                          // count windows, by turns
     int near_idx[kTilesPerGroup][kTileNear];
-    int near_n[kTilesPerGroup];                          // more than kTileNear: every near star of the block
+    int near_n[kTilesPerGroup];
+    // of a tile with more near stars than that: which of the block's, 64 of its lists a word
+    unsigned long long near_of[kTilesPerGroup][kBlockNear / 64];
 };
 
 // Image angle of lattice index base + off, base and off given as doubles:
@@ -617,44 +620,61 @@ __device__ __forceinline__ void near_star(double sx, double sy, double sm, const
     }
 }
 
+// Entry e of a block's near lists, one after the other; before[w] is the first
+// entry of wave w's list.
+__device__ __forceinline__ int block_near(const BlockFar *f, const int (&before)[kWaves], int e) {
+    const int w = (e >= before[1]) + (e >= before[2]) + (e >= before[3]);
+    return f->outer_idx[w][e - (w == 0 ? 0 : w == 1 ? before[1] : w == 2 ? before[2] : before[3])];
+}
+
 // The stars a tile sums directly, one after the other, uniform in the wave:
-// all stars when the block's lists have overflowed, the block's near stars
-// (each wave's list of the block pass in turn) when the tile's list has, else
-// the tile's near stars; body(x, y, m).
+// all stars when the block's lists have overflowed, else the tile's near
+// stars; body(x, y, m).  They come 64 at a time, indices in the lanes, and the
+// next star's record is loaded while the current one is summed.  A tile's own
+// list gives the indices without a trip to memory; one with more near stars
+// than that takes the block's lists, of which near_of marks its own (40000
+// stars, 2000^2 rays, blocks of 2 x 2 tiles of 257 near stars and more: 523 us
+// a map, 1350 when such a tile summed all of its block's).
 template <class Body>
 __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, const ConstStar *st, const BlockFar *f,
                                                 bool all, int n_stars, Body body) {
-    const int cnt = all ? n_stars : uniform(sh.near_n[t]);
-    if (!all && cnt <= kTileNear) {
-        // 64 indices at a time in the lanes; the next star's record is loaded
-        // while the current one is summed
-        for (int i0 = 0; i0 < cnt; i0 += 64) {
-            const int m = cnt - i0 < 64 ? cnt - i0 : 64;
-            const int idx = sh.near_idx[t][i0 + threadIdx.x % 64];
-            int k = __builtin_amdgcn_readlane(idx, 0);
-            double sx = st[k].x, sy = st[k].y, sm = st[k].m;
-            for (int i = 0; i < m; ++i) {
-                asm volatile("" : "+s"(sx), "+s"(sy), "+s"(sm));   // the current record is here
-                k = __builtin_amdgcn_readlane(idx, i + 1 < m ? i + 1 : i);
-                const double nx = st[k].x, ny = st[k].y, nm = st[k].m;
-                __builtin_amdgcn_sched_barrier(0);                 // the loads stay ahead of the sum
-                body(sx, sy, sm);
-                sx = nx;
-                sy = ny;
-                sm = nm;
-            }
-        }
-        return;
-    }
     if (all) {
-        for (int k = 0; k < cnt; ++k) body(st[k].x, st[k].y, st[k].m);
+        for (int k = 0; k < n_stars; ++k) body(st[k].x, st[k].y, st[k].m);
         return;
     }
-    for (int w = 0; w < kWaves; ++w) {
-        const int in_list = uniform(f->outer_n[w]);
-        for (int i = 0; i < in_list; ++i) {
-            const int k = uniform(f->outer_idx[w][i]);
-            body(st[k].x, st[k].y, st[k].m);
+    const int lane = threadIdx.x % 64, cnt = uniform(sh.near_n[t]);
+    const bool own = cnt <= kTileNear;
+    int before[kWaves] = {}, total = 0;
+    if (!own)
+        for (int w = 0; w < kWaves; ++w) {
+            before[w] = total;
+            total += uniform(f->outer_n[w]);
+        }
+    const int entries = own ? cnt : total;
+    for (int i0 = 0; i0 < entries; i0 += 64) {   // uniform
+        int idx = 0;
+        unsigned long long left;   // which of the 64 are the tile's (uniform)
+        if (own) {
+            idx = sh.near_idx[t][i0 + lane];
+            left = entries - i0 < 64 ? (1ull << (entries - i0)) - 1ull : ~0ull;
+        } else {
+            left = (unsigned long long)uniform64((int64_t)sh.near_of[t][i0 / 64]);
+            if (i0 + lane < entries) idx = block_near(f, before, i0 + lane);
+        }
+        if (left == 0) continue;
+        int k = __builtin_amdgcn_readlane(idx, __builtin_ctzll(left));
+        double sx = st[k].x, sy = st[k].y, sm = st[k].m;
+        while (left != 0) {
+            asm volatile("" : "+s"(sx), "+s"(sy), "+s"(sm));   // the current record is here
+            const unsigned long long rest = left & (left - 1);
+            k = __builtin_amdgcn_readlane(idx, __builtin_ctzll(rest != 0 ? rest : left));
+            const double nx = st[k].x, ny = st[k].y, nm = st[k].m;
+            __builtin_amdgcn_sched_barrier(0);                 // the loads stay ahead of the sum
+            body(sx, sy, sm);
+            sx = nx;
+            sy = ny;
+            sm = nm;
+            left = rest;
         }
     }
 }
@@ -664,7 +684,7 @@ __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, con
 // L = 2 the whole block, for L = 1 the one tile), in three phases:
 //   1. One wave per tile re-centres the block's polynomial on its tile,
 //      re-tests the block's near stars (far ones join the polynomial, near
-//      ones go to the tile's list) and sums the lanes' series.  A wave does
+//      ones go to the tile's list, and are marked in the block's) and sums the lanes' series.  A wave does
 //      this alone, without a barrier: with the four waves sharing each tile's
 //      stars, every wave still had to sum all 50 components, four times the
 //      work, between two barriers a tile.
@@ -730,12 +750,16 @@ __global__ __launch_bounds__(kThreads, 3) void expansion_tile_kernel(ShootParams
 
     // --- phase 1
     if (L == 1) {
-        // the block is the tile: its near stars, in one list
+        // the block is the tile: its near stars, in one list, or every one of the block's
         if (threadIdx.x == 0) sh.near_n[0] = n_outer;
         if (!overflow && n_outer <= kTileNear)
             for (int w = 0; w < kWaves; ++w)
                 for (int i = threadIdx.x; i < uniform(f->outer_n[w]); i += kThreads)
                     sh.near_idx[0][before[w] + i] = f->outer_idx[w][i];
+        if (threadIdx.x < kBlockNear / 64) {
+            const int in = n_outer - 64 * (int)threadIdx.x;   // entries of this word
+            sh.near_of[0][threadIdx.x] = in >= 64 ? ~0ull : in > 0 ? (1ull << in) - 1ull : 0ull;
+        }
     } else if (!overflow && wave < G) {
         const int t = t_begin + wave;
         double bcx, bcy, brho, cx, cy, rho;
@@ -751,8 +775,7 @@ __global__ __launch_bounds__(kThreads, 3) void expansion_tile_kernel(ShootParams
             bool near = false;
             int k = 0;
             if (e < n_outer) {
-                const int w = (e >= before[1]) + (e >= before[2]) + (e >= before[3]);
-                k = f->outer_idx[w][e - (w == 0 ? 0 : w == 1 ? before[1] : w == 2 ? before[2] : before[3])];
+                k = block_near(f, before, e);
                 const double sx = st[k].x, sy = st[k].y, sm = st[k].m;
                 const double dx = cx - sx, dy = cy - sy;
                 const double d2 = dx * dx + dy * dy;
@@ -776,6 +799,7 @@ __global__ __launch_bounds__(kThreads, 3) void expansion_tile_kernel(ShootParams
                 if (pos < kTileNear) sh.near_idx[wave][pos] = k;
             }
             found += __popcll(ball);
+            if (lane == 0) sh.near_of[wave][base / 64] = ball;
         }
         if (lane == 0) sh.near_n[wave] = found;
         const double v = wave_reduce_coeffs(acc);
@@ -789,11 +813,10 @@ __global__ __launch_bounds__(kThreads, 3) void expansion_tile_kernel(ShootParams
             S = recentre_step(S, sh.block[r + j - 1], sx * kInverse.f[j], sy * kInverse.f[j]);
         const double br = int_pow(rho * inv_brho, r);
         if (lane < kAlpha) sh.tile[wave][lane] = lane <= kOrder ? make_double2(S.x * br, S.y * br) : make_double2(0.0, 0.0);
-        // plus the re-tested far stars', unless the list has overflowed: then
-        // the block's near stars are all summed directly
+        // plus the re-tested far stars'
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the stores above, by other lanes
         __builtin_amdgcn_wave_barrier();
-        if (found <= kTileNear && lane < 2 * (kOrder + 1)) {
+        if (lane < 2 * (kOrder + 1)) {
             double *d = reinterpret_cast<double *>(sh.tile[wave]);
             d[lane] += v * kFactorial.f[lane / 2];
         }
