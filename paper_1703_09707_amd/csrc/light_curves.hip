@@ -297,10 +297,17 @@ __global__ __launch_bounds__(kLcThreads, 8) void light_curve_track_kernel(
     int64_t n_tracks, int64_t n_chunks, int chunks_per_track, int n_samples, double inv_n1,
     double *__restrict__ out) {
 #pragma clang fp contract(off)
-    // Workgroups go to the 8 XCDs in turn; each XCD takes a contiguous eighth
-    // of them, so that tracks next to each other in the order share an L2.
-    const unsigned eighth = gridDim.x / 8;   // whole rounds; the rest keep their place
-    const unsigned block = blockIdx.x < 8 * eighth ? blockIdx.x % 8 * eighth + blockIdx.x / 8 : blockIdx.x;
+    // Workgroups go to the 8 XCDs in turn; each XCD takes every eighth of 32
+    // contiguous parts, so that tracks next to each other in the order share an
+    // L2, and each XCD has tracks of the map's middle and of its edges: those
+    // that leave the map cost less (2^18 tracks of 256 samples as long as the
+    // map is wide, midpoints all over it: 425 us, 477 with a contiguous eighth
+    // an XCD; 2^20 that stay inside: 770 and 768).
+    constexpr unsigned kXcds = 8, kParts = 4;
+    const unsigned part = gridDim.x / (kXcds * kParts), turn = blockIdx.x / kXcds;
+    const unsigned block = blockIdx.x < kXcds * kParts * part   // whole parts; the rest keep their place
+                               ? (turn / part * kXcds + blockIdx.x % kXcds) * part + turn % part
+                               : blockIdx.x;
     const int64_t chunk = wave_uniform((int64_t)block * (kLcThreads / 64) + threadIdx.x / 64);
     if (chunk >= n_chunks) return;   // uniform in the wave
     const int64_t tp = chunks_per_track == 1 ? chunk
@@ -376,7 +383,9 @@ __global__ __launch_bounds__(kLcThreads, 8) void light_curve_track_kernel(
             return;
         }
     }
-    // a sample at a time (SMALL: rare), or all at once
+    // SMALL: a sample at a time (all at once is no faster, the other waves
+    // hide the latency: 2^18 tracks as above 476 us both, 300000 of 100
+    // samples 142 for 133); else all at once
     constexpr int kAtOnce = SMALL ? 1 : kSpt;
 #pragma unroll 1
     for (int e0 = 0; e0 < kSpt; e0 += kAtOnce) {
@@ -417,7 +426,7 @@ __global__ __launch_bounds__(kLcThreads, 8) void light_curve_track_kernel(
 // kDirections tracks or more on average, each cell's are sorted again by
 // direction: tracks side by side then read the same rows all along, not only
 // near their midpoints (2^20 tracks of 250 samples, 205 of 1024 pixels long:
-// curves 858 -> 689 us, 671 with the XCDs' eighths in the kernel above).
+// curves 858 -> 689 us, 671 with the XCDs' parts in the kernel above).
 constexpr int kCellPx = 16;
 constexpr int kMaxCellsPerSide = 2048;
 constexpr int kScanThreads = 1024;
