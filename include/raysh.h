@@ -164,10 +164,11 @@ int64_t raysh_n_stars(const raysh_ctx *ctx);
  * raysh_set_tile means min(share, 4)).  RAYSH_FP32_BULK: `star_tile` stars
  * are staged in LDS per pass (the FP32 partial sums are flushed into FP64
  * after each pass), and `share` must be 0.  EINVAL if the shape is not
- * compiled into the library.  Until raysh_set_tile sets a RAYSH_FP64 shape,
- * lattices that would leave compute units idle in the context's shape run in
- * a form in which a workgroup's 4 to 16 waves share one tile and split its
- * stars into contiguous runs, added in order after the macro term.
+ * compiled into the library.  Until raysh_set_tile or the tuner sets a
+ * RAYSH_FP64 shape, lattices that would leave compute units idle in the
+ * context's shape run in a form in which a workgroup's 4 to 16 waves share one
+ * tile and split its stars into contiguous runs, added in order after the
+ * macro term.
  */
 int raysh_set_tile(raysh_ctx *ctx, int precision, int cx, int cy, int share, int star_tile);
 
@@ -243,8 +244,9 @@ int raysh_get_tile(const raysh_ctx *ctx, int precision, int *cx, int *cy, int *s
  * raysh_autotune: time every launch shape compiled for `precision` on a
  * sample of the ray block mapped into a scratch map (one warm-up, then the
  * median of three launches), keep the one with the shortest predicted time
- * for the whole block in the context (as raysh_set_tile would) and return it
- * through the optional out-pointers.  A shape's sample is a central part of
+ * for the whole block in the context (as raysh_set_tile would: from then on
+ * every lattice runs in it) and return it through the optional out-pointers.
+ * A shape's sample is a central part of
  * the block made of whole tiles, in whole rounds of the workgroups the
  * device holds at once (until about 1e11 ray-star interactions or the
  * block's own rounds); its time per round, times the rounds the whole block
@@ -269,7 +271,7 @@ int raysh_autotune(raysh_ctx *ctx, const raysh_rays *rays, const raysh_pixels *p
  * share of 1e11 ray-star interactions per set, sides in whole multiples of
  * 128 rays so that no compiled tile is ragged in it, at most the block),
  * mapped into scratch maps; the fastest is set in every
- * context (raysh_map_batch uses the shape of sets[0]) and returned through
+ * context, as raysh_set_tile would (raysh_map_batch uses the shape of sets[0]) and returned through
  * the optional out-pointers.  The cache is that of raysh_autotune, keyed
  * also by "batch" and by the mean star count of the sets.  Synchronous.
  * Errors as raysh_map_batch; ENOMEM if the scratch maps cannot be

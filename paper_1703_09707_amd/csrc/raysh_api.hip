@@ -478,8 +478,7 @@ int raysh_set_tile(raysh_ctx *ctx, int precision, int cx, int cy, int share, int
     if (!supported)
         return set_error(RAYSH_EINVAL, "tile shape (%d, %d, %d, %d) is not built for precision %d", cx, cy,
                     share, star_tile, precision);
-    ctx->shape[precision] = t;
-    if (precision == RAYSH_FP64) ctx->fixed_shape = true;
+    set_shape(ctx, precision, t);
     return set_ok();
 }
 

@@ -18,7 +18,7 @@ struct raysh_ctx {
     unsigned long long *h_counter = nullptr;   // pinned
     // default launch shapes: the fastest on MI355X for the 16384-star workload
     raysh::TileShape shape[2] = {{8, 4, 16, 1}, {4, 4, 0, 128}};
-    bool fixed_shape = false;              // FP64 one pass: shape[0] whatever the lattice (raysh_set_tile)
+    bool fixed_shape = false;              // FP64 one pass: shape[0] whatever the lattice (set_shape)
     int star_parts = 1;                    // FP64 split of each ray's star sum (0 = automatic)
     double theta_open = 0.25;              // far-star criterion of RAYSH_FP64_EXPANSION
     int expansion_block = 0;               // tiles per side of its workgroups (0 = automatic)
@@ -47,6 +47,12 @@ int validate_device_ptr(const void *ptr, size_t bytes, int device, const char *n
 // Lens, rays and window of one call packed for the kernels (outputs unset).
 void fill_shoot_params(raysh::ShootParams &p, const raysh_ctx *c, const raysh_rays *r,
                        const raysh_pixels *w);
+
+// The launch shape of raysh_set_tile and the tuner: from now on every lattice's.
+inline void set_shape(raysh_ctx *c, int precision, const raysh::TileShape &t) {
+    c->shape[precision] = t;
+    if (precision == RAYSH_FP64) c->fixed_shape = true;
+}
 
 // Drop captured batch launches that reference ctx (called by raysh_free).
 void raysh_forget_batches(const raysh_ctx *ctx);

@@ -279,7 +279,7 @@ extern "C" int raysh_autotune(raysh_ctx *ctx, const raysh_rays *rays, const rays
         if (code != RAYSH_OK) return code;
         if (cache_path) cache_store(cache_path, key, best, best_ms);
     }
-    ctx->shape[precision] = best;
+    set_shape(ctx, precision, best);
     report(best, cx, cy, share, star_tile);
     return set_ok();
 }
@@ -361,7 +361,7 @@ extern "C" int raysh_autotune_batch(raysh_ctx *const *sets, int n_sets, const ra
         }
         if (cache_path) cache_store(cache_path, key, best, best_ms);
     }
-    for (int s = 0; s < n_sets; ++s) sets[s]->shape[precision] = best;
+    for (int s = 0; s < n_sets; ++s) set_shape(sets[s], precision, best);
     report(best, cx, cy, share, star_tile);
     return set_ok();
 }

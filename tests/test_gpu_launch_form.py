@@ -1,0 +1,69 @@
+"""Which form a one-pass FP64 launch runs in: the shape that raysh_set_tile or
+the tuner has set, else the lattice's own (waves that share a tile where the
+context's shape would leave compute units idle)."""
+import numpy as np
+import pytest
+
+from paper_1703_09707_amd import raysh as R
+
+pytestmark = pytest.mark.gpu
+
+PIX = (-0.9, -0.8, 1.7 / 45, 1.9 / 52, 45, 52)
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    if not t.cuda.is_available():
+        pytest.fail("GPU tests need a ROCm GPU")
+    return t
+
+
+def _rays(nx, ny):
+    return (-1.25, -1.25, 2.5 / nx, 2.5 / nx, nx, ny, 0, 0)
+
+
+def _lens(n, seed=0):
+    rng = np.random.default_rng(n + seed)
+    return (0.1, 0.1, -0.05, rng.uniform(-3, 3, n), rng.uniform(-3, 3, n), rng.uniform(0.01, 0.05, n))
+
+
+def _shoot(ctx, rays):
+    return [t.cpu().numpy() for t in ctx.shoot(rays, "fp64", PIX)]
+
+
+def _same(a, b):
+    for x, y in zip(a, b):
+        np.testing.assert_array_equal(x, y)
+
+
+def _set(ctx, t):
+    ctx.set_tile("fp64", t[0], t[1], share=t[2], star_tile=t[3])
+
+
+@pytest.mark.parametrize("nx,ny", [(500, 490), (100, 100)])
+def test_tuned_shape_runs(torch, tmp_path, nx, ny):
+    """After raysh_autotune, and after a hit of its cache, the shape it returns
+    is the one that runs, on a lattice whose own form would be another."""
+    rays, lens = _rays(nx, ny), _lens(300)
+    cache = str(tmp_path / "cache")
+    for _ in ("timed", "cached"):
+        with R.Context(lens) as ctx, R.Context(lens) as fixed:
+            t = ctx.autotune(rays, PIX, "fp64", cache_path=cache)
+            _set(fixed, t)
+            _same(_shoot(ctx, rays), _shoot(fixed, rays))
+
+
+def test_batch_tuned_shape_runs(torch):
+    rays = [_rays(300, 200), _rays(120, 500)]
+    lenses = [_lens(200, 1), _lens(150, 2)]
+    ctxs = [R.Context(l) for l in lenses]
+    try:
+        t = R.autotune_batch(ctxs, rays, [PIX, PIX], "fp64")
+        for ctx, lens, r in zip(ctxs, lenses, rays):
+            with R.Context(lens) as fixed:
+                _set(fixed, t)
+                _same(_shoot(ctx, r), _shoot(fixed, r))
+    finally:
+        for c in ctxs:
+            c.close()
