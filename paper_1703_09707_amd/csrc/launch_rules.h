@@ -1,0 +1,79 @@
+// Rules by which a launch is chosen from sizes alone: plain host C++, so that
+// they can be checked over extents that no test could run.
+#pragma once
+
+#include <cstdint>
+
+namespace raysh {
+
+// Launch shapes selectable per call (the autotuner's search space).
+struct TileShape {
+    int cx, cy;      // rays per lane along x and y
+    int share;       // r^2 values sharing one reciprocal (FP64 path)
+    int star_tile;   // FP64: consecutive stars among them (the rest are the lane's
+                     // neighbouring rays); FP32-bulk: stars staged in LDS per pass
+};
+
+// A one-dimensional grid that HIP launches: fewer than 2^32 threads.
+inline bool grid_fits(int64_t blocks, int threads) { return blocks <= (((int64_t)1 << 32) - 1) / threads; }
+
+// Forms of the one-pass FP64 kernel in which the waves of a workgroup share a
+// tile of 8 cx x 8 cy rays (waves_fp64_kernel): cx, cy, share, star_tile, waves.
+#define RAYSH_FP64_WAVES(X) \
+    X(8, 4, 16, 1, 4)       \
+    X(4, 4, 16, 1, 8)       \
+    X(4, 2, 8, 1, 16)       \
+    X(2, 2, 4, 1, 16)
+
+inline int64_t tiles_of(int64_t nx, int64_t ny, int w, int h) { return ((nx + w - 1) / w) * ((ny + h - 1) / h); }
+
+// Time of the busiest compute unit, in instructions of a lane (64 lanes a
+// cycle), of a launch whose workgroups each take a tile of w x h rays and
+// `once` besides the star sum.  A ray and star take 6 instructions, a lane's
+// column and row one and two (shared by its rays), a reciprocal four with its
+// tree, and a mass per ray half of one.  A unit takes whole tiles, and the
+// last of them runs partly alone (0.15 of a tile: 2048^2 rays and 10000 stars
+// take 8.63 ms in 2 tiles a unit and 8.03 in 8, 4096^2 rays and 16384 stars
+// 52.7 in 8 and 51.8 in 32); a unit with one wave a SIMD for all its tiles
+// issues 0.8 times as fast.
+inline double busiest_unit(int64_t nx, int64_t ny, int64_t n_stars, const TileShape &t, int w, int h, int waves,
+                           double once, int n_cu) {
+    const int64_t mine = (tiles_of(nx, ny, w, h) + n_cu - 1) / n_cu;
+    const double v = 6.0 + 1.0 / t.cy + 2.0 / t.cx + 4.0 / t.share + (t.star_tile > 1 ? 0.5 : 0.0);
+    const double last = mine * waves >= 8 ? 0.15 : 0.25;
+    return ((double)mine + last) * (double)n_stars * w * h * v + (double)mine * once;
+}
+
+// A tile's epilogue, in the same unit: 16 us for 8192 rays, about 4 for each
+// shape of waves_fp64_kernel (1000^2 rays and 10 stars: 21 us in one such
+// tile a unit, 11.6 in two of 2048 rays, 41 in eight of 512).
+constexpr double kOncePerTile = 2.4e6, kOnceShared = 6.5e5;
+
+// One pass in the fastest form for the lattice: `t` (the shape for lattices
+// that fill the device many times over: -1) or the waves of a workgroup sharing
+// a tile (the form's place in RAYSH_FP64_WAVES), whichever keeps the busiest
+// compute unit busy least and can be launched.  Measured (us, t and the form
+// chosen): 100 stars and 1000^2 rays 64 -> 31, 1000 and 500^2 458 -> 62, 1000
+// and 250^2 457 -> 25, 3000 and 100^2 1343 -> 58, 10000 and 2048^2 8630 ->
+// 8030; 1000 and 8192^2 stay with t (12.70 ms against 12.91, its epilogue
+// being cheaper a ray).
+inline int waves_form(int64_t nx, int64_t ny, int64_t n_stars, const TileShape &t, int n_cu) {
+    if (n_cu < 1) n_cu = 1;
+    double best = 0.99 * busiest_unit(nx, ny, n_stars, t, 16 * t.cx, 16 * t.cy, 4, kOncePerTile, n_cu);
+    int form = -1, i = 0;
+#define RAYSH_CASE(CX, CY, S, NS, W)                                                                      \
+    if (grid_fits(tiles_of(nx, ny, 8 * CX, 8 * CY), 64 * W)) {                                            \
+        const double cost =                                                                               \
+            busiest_unit(nx, ny, n_stars, TileShape{CX, CY, S, NS}, 8 * CX, 8 * CY, W, kOnceShared, n_cu); \
+        if (cost < best) {                                                                                \
+            best = cost;                                                                                  \
+            form = i;                                                                                     \
+        }                                                                                                 \
+    }                                                                                                     \
+    ++i;
+    RAYSH_FP64_WAVES(RAYSH_CASE)
+#undef RAYSH_CASE
+    return form;
+}
+
+}  // namespace raysh

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch_rules.h"
 #include "raysh.h"
 
 namespace raysh {
@@ -55,14 +56,6 @@ struct BatchArgs {
     int32_t n_sets;
     int64_t total_items;
     unsigned long long *queue;   // next item to hand out; zero before launch
-};
-
-// Launch shapes selectable per call (the autotuner's search space).
-struct TileShape {
-    int cx, cy;      // rays per lane along x and y
-    int share;       // r^2 values sharing one reciprocal (FP64 path)
-    int star_tile;   // FP64: consecutive stars among them (the rest are the lane's
-                     // neighbouring rays); FP32-bulk: stars staged in LDS per pass
 };
 
 // Launchers (shoot_fp64.hip, shoot_fp32.hip).  Return hipSuccess or the

@@ -681,35 +681,6 @@ hipError_t launch(const ShootParams &p, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Shapes of waves_fp64_kernel.
-#define RAYSH_FP64_WAVES(X) \
-    X(8, 4, 16, 1, 4)       \
-    X(4, 4, 16, 1, 8)       \
-    X(4, 2, 8, 1, 16)       \
-    X(2, 2, 4, 1, 16)
-
-// Time of the busiest compute unit, in instructions of a lane (64 lanes a
-// cycle), of a launch whose workgroups each take a tile of w x h rays and
-// `once` besides the star sum.  A ray and star take 6 instructions, a lane's
-// column and row one and two (shared by its rays), a reciprocal four with its
-// tree, and a mass per ray half of one.  A unit takes whole tiles, and the
-// last of them runs partly alone (0.15 of a tile: 2048^2 rays and 10000 stars
-// take 8.63 ms in 2 tiles a unit and 8.03 in 8, 4096^2 rays and 16384 stars
-// 52.7 in 8 and 51.8 in 32); a unit with one wave a SIMD for all its tiles
-// issues 0.8 times as fast.
-double busiest_unit(const ShootParams &p, const TileShape &t, int w, int h, int waves, double once, int n_cu) {
-    const int64_t tiles = ((p.nx + w - 1) / w) * ((p.ny + h - 1) / h);
-    const int64_t mine = (tiles + n_cu - 1) / n_cu;
-    const double v = 6.0 + 1.0 / t.cy + 2.0 / t.cx + 4.0 / t.share + (t.star_tile > 1 ? 0.5 : 0.0);
-    const double last = mine * waves >= 8 ? 0.15 : 0.25;
-    return ((double)mine + last) * (double)p.n_stars * w * h * v + (double)mine * once;
-}
-
-// A tile's epilogue, in the same unit: 16 us for 8192 rays, about 4 for each
-// shape of waves_fp64_kernel (1000^2 rays and 10 stars: 21 us in one such
-// tile a unit, 11.6 in two of 2048 rays, 41 in eight of 512).
-constexpr double kOncePerTile = 2.4e6, kOnceShared = 6.5e5;
-
 template <int CX, int CY, int SHARE, int NS, int W>
 hipError_t launch_waves(const ShootParams &p, hipStream_t s) {
     ShootParams q = p;
@@ -790,28 +761,14 @@ hipError_t launch_shoot_fp64(const ShootParams &p, const TileShape &t, hipStream
     return hipErrorInvalidValue;
 }
 
-// One pass in the fastest form for the lattice: `t` (the shape for lattices
-// that fill the device many times over) or the waves of a workgroup sharing a
-// tile, whichever keeps the busiest compute unit busy least.  Measured (us, t
-// and the form chosen): 100 stars and 1000^2 rays 64 -> 31, 1000 and 500^2
-// 458 -> 62, 1000 and 250^2 457 -> 25, 3000 and 100^2 1343 -> 58, 10000 and
-// 2048^2 8630 -> 8030; 1000 and 8192^2 stay with t (12.70 ms against 12.91,
-// its epilogue being cheaper a ray).
 hipError_t launch_shoot_fp64_auto(const ShootParams &p, const TileShape &t, int n_cu, hipStream_t s) {
-    if (n_cu < 1) n_cu = 1;
-    double best = 0.99 * busiest_unit(p, t, tile_width(t), tile_height(t), kThreads / 64, kOncePerTile, n_cu);
-    hipError_t (*run)(const ShootParams &, hipStream_t) = nullptr;
-#define RAYSH_CASE(CX, CY, S, NS, W)                                                                     \
-    {                                                                                                    \
-        const double cost = busiest_unit(p, TileShape{CX, CY, S, NS}, 8 * CX, 8 * CY, W, kOnceShared, n_cu); \
-        if (cost < best) {                                                                               \
-            best = cost;                                                                                 \
-            run = launch_waves<CX, CY, S, NS, W>;                                                        \
-        }                                                                                                \
-    }
+    const int form = waves_form(p.nx, p.ny, p.n_stars, t, n_cu);
+    int i = 0;
+#define RAYSH_CASE(CX, CY, S, NS, W) \
+    if (form == i++) return launch_waves<CX, CY, S, NS, W>(p, s);
     RAYSH_FP64_WAVES(RAYSH_CASE)
 #undef RAYSH_CASE
-    return run ? run(p, s) : launch_shoot_fp64(p, t, s);
+    return launch_shoot_fp64(p, t, s);
 }
 
 hipError_t launch_split_fp64(const ShootParams &p, const TileShape &t, int parts, double2 *partial,

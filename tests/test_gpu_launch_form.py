@@ -67,3 +67,19 @@ def test_batch_tuned_shape_runs(torch):
     finally:
         for c in ctxs:
             c.close()
+
+
+def test_wide_lattice_of_few_rows(torch):
+    """2^27 columns: the form with 1024 threads for 32 x 16 rays would need
+    2^32 threads.  The map equals that of a set shape."""
+    nx = (1 << 27) + 77
+    rays = (-1.25, -0.3, 2.5 / nx, 0.3, nx, 2, 0, 0)
+    pix = (-2.0, -2.0, 0.05, 0.05, 80, 80)
+    with R.Context(_lens(150)) as ctx:
+        m, n = ctx.map(rays, pix, "fp64", n_binned=True)
+        _set(ctx, (8, 4, 16, 1))
+        w, nw = ctx.map(rays, pix, "fp64", n_binned=True)
+    # rays within a rounding of a pixel's edge (1e-14 of its 0.05) may go either way
+    assert abs(int(n) - int(nw)) <= 10
+    assert int((m - w).abs().sum()) <= 20
+    assert int(n) == int(m.sum(dtype=torch.int64)) > nx // 2

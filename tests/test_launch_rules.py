@@ -1,0 +1,79 @@
+"""The rules that choose a launch from sizes alone (csrc/launch_rules.h), over
+extents that no test could run: built as plain C++ on the host."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1703_09707_amd", "csrc")
+MAX_RAYS = 2 ** 31 - 1   # of a lattice block
+CU = 256
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstring>
+#include "launch_rules.h"
+using namespace raysh;
+int main() {
+    char what[32];
+    while (std::scanf("%31s", what) == 1) {
+        long long nx, ny, n;
+        if (!std::strcmp(what, "waves")) {   // form, and the threads of its grid (0: the context's shape)
+            if (std::scanf("%lld %lld %lld", &nx, &ny, &n) != 3) return 1;
+            const int form = waves_form(nx, ny, n, TileShape{8, 4, 16, 1}, 256);
+            long long threads = 0;
+            int i = 0;
+#define RAYSH_CASE(CX, CY, S, NS, W) \
+            if (form == i++) threads = tiles_of(nx, ny, 8 * CX, 8 * CY) * 64 * W;
+            RAYSH_FP64_WAVES(RAYSH_CASE)
+#undef RAYSH_CASE
+            std::printf("%d %lld\n", form, threads);
+        } else {
+            return 2;
+        }
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++") or "/opt/rocm/bin/amdclang++"
+    d = tmp_path_factory.mktemp("rules")
+    src, out = str(d / "rules.cpp"), str(d / "rules")
+    with open(src, "w") as f:
+        f.write(PROGRAM)
+    subprocess.run([cxx, "-O1", "-std=c++17", "-Wall", "-I", CSRC, src, "-o", out], check=True)
+
+    def ask(lines):
+        r = subprocess.run([out], input="\n".join(" ".join(map(str, l)) for l in lines), capture_output=True,
+                           text=True, check=True)
+        return [tuple(map(float, l.split())) for l in r.stdout.splitlines()]
+    return ask
+
+
+def _extents():
+    sides = sorted({s + d for k in range(31) for s in (1 << k,) for d in (-1, 0, 1)} | {3, 15, 17, 1000, MAX_RAYS})
+    return [(nx, ny) for nx in sides for ny in sides if 1 <= nx and 1 <= ny and nx * ny <= MAX_RAYS]
+
+
+@pytest.mark.parametrize("stars", [0, 1, 50, 106, 300, 3000, 100_000, 1 << 28])
+def test_waves_forms_fit_their_grid(rules, stars):
+    """Every lattice that is accepted gets a form that HIP launches (fewer than
+    2^32 threads): with 1024 threads for 32 x 16 rays, a lattice of a few rows
+    and 2^27 columns does not."""
+    ext = _extents()
+    got = rules([("waves", nx, ny, stars) for nx, ny in ext])
+    assert len(got) == len(ext)
+    for (nx, ny), (form, threads) in zip(ext, got):
+        assert threads < 2 ** 32, (nx, ny, stars, form)
+
+
+def test_waves_forms_of_small_lattices(rules):
+    """The lattices the forms were measured on keep them."""
+    got = rules([("waves", 1000, 1000, 100), ("waves", 250, 250, 1000), ("waves", 100, 100, 3000),
+                 ("waves", 8192, 8192, 1000), ("waves", 8192, 8192, 16384)])
+    assert [int(f) for f, _ in got][0] == 0 and all(f > 0 for f, _ in got[1:3])
+    assert [int(f) for f, _ in got][3:] == [-1, -1]
