@@ -173,7 +173,7 @@ extern "C" int raysh_log_mag_histogram(const int32_t *counts, int32_t nx, int32_
 
     hipStream_t s = (hipStream_t)hip_stream;
     double *tmp = (double *)workspace;                      // ny * wx
-    if (rx <= kTapsMaxRadius && ry <= kTapsMaxRadius) {
+    if (slides(rx, ry, wx, ny)) {
         unsigned *done = (unsigned *)(tmp + (size_t)ny * wx);   // workgroups of the column pass that have finished
         launch_smooth_rows(s, counts, nx, ny, norm, sigma, px, rx, wx, tmp, (unsigned *)bin_counts, nbins, done);
         const int R = slide_rows_per_thread((int64_t)wx * wy);

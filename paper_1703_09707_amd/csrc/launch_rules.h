@@ -76,4 +76,11 @@ inline int waves_form(int64_t nx, int64_t ny, int64_t n_stars, const TileShape &
     return form;
 }
 
+// Workgroups of smooth_rows_slide_kernel (256 outputs of 4 rows each) and of
+// disk_prefix_kernel (one, and one for every 4 rows).  Both take a wave per
+// row however short the row is, so a map of few columns and 2^26 rows or more
+// exceeds the grid, where a thread per output does not.
+inline int64_t smooth_row_blocks(int wx, int ny) { return ((wx + (int64_t)255) / 256) * ((ny + (int64_t)3) / 4); }
+inline int64_t disk_prefix_blocks(int ny) { return 1 + (ny + (int64_t)3) / 4; }
+
 }  // namespace raysh

@@ -688,7 +688,7 @@ extern "C" int raysh_source_map(const int32_t *counts, int32_t nx, int32_t ny, d
     hipStream_t s = (hipStream_t)hip_stream;
     const int64_t n_out = (int64_t)wx * wy;
     const unsigned blocks_out = (unsigned)((n_out + kLcThreads - 1) / kLcThreads);
-    if (profile == RAYSH_SOURCE_GAUSSIAN && rx <= kTapsMaxRadius && ry <= kTapsMaxRadius) {
+    if (profile == RAYSH_SOURCE_GAUSSIAN && slides(rx, ry, wx, ny)) {
         double *tmp = (double *)workspace;                  // ny * wx
         launch_smooth_rows(s, counts, nx, ny, norm, size, px, rx, wx, tmp);
         const int R = slide_rows_per_thread(n_out);
@@ -714,10 +714,10 @@ extern "C" int raysh_source_map(const int32_t *counts, int32_t nx, int32_t ny, d
         long long *n_taps = (long long *)workspace;
         int *half = (int *)(n_taps + 1);                    // 2 ry + 1 < ny
         long long *prefix = n_taps + 1 + (2 * ry + 2) / 2;  // nx * ny: within the workspace, as 2 ry + 2 <= ny
-        const bool by_prefix = disk_by_prefix(rx, ry);
-        const unsigned row_blocks = by_prefix ? (unsigned)((ny + kLcThreads / 64 - 1) / (kLcThreads / 64)) : 0;
-        hipLaunchKernelGGL(disk_prefix_kernel, dim3(1 + row_blocks), dim3(kLcThreads), 0, s, counts, nx, ny, size, px,
-                           py, rx, ry, half, n_taps, prefix);
+        const int64_t prefix_blocks = raysh::disk_prefix_blocks(ny);
+        const bool by_prefix = disk_by_prefix(rx, ry) && raysh::grid_fits(prefix_blocks, kLcThreads);
+        hipLaunchKernelGGL(disk_prefix_kernel, dim3(by_prefix ? (unsigned)prefix_blocks : 1u), dim3(kLcThreads), 0, s,
+                           counts, nx, ny, size, px, py, rx, ry, half, n_taps, prefix);
         if (by_prefix)
             hipLaunchKernelGGL(disk_map_kernel, dim3(blocks_out), dim3(kLcThreads), 0, s, prefix, nx, norm, rx, ry,
                                half, n_taps, wx, wy, mu_s);

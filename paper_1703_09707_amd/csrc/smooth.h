@@ -13,6 +13,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "launch_rules.h"
+
 namespace {
 
 constexpr int kSmoothThreads = 256;
@@ -245,12 +247,19 @@ inline unsigned slide_blocks(int wx, int wy, int R) {
     return (unsigned)((threads + kSmoothThreads - 1) / kSmoothThreads);
 }
 
+// Whether the two sliding passes serve these radii and this map.
+inline bool slides(int rx, int ry, int wx, int ny) {
+    return rx <= kTapsMaxRadius && ry <= kTapsMaxRadius &&
+           raysh::grid_fits(raysh::smooth_row_blocks(wx, ny), kSmoothThreads);
+}
+
 inline void launch_smooth_rows(hipStream_t s, const int32_t *counts, int nx, int ny, double norm, double sigma,
                                double pixel, int rx, int wx, double *tmp, unsigned *zero = nullptr, int n_zero = 0,
                                unsigned *done = nullptr) {
-    constexpr int kRows = kSmoothThreads / 64;
-    const unsigned blocks = (unsigned)((wx + kRowSpan - 1) / kRowSpan) * (unsigned)((ny + kRows - 1) / kRows);
-    hipLaunchKernelGGL(smooth_rows_slide_kernel, dim3(blocks), dim3(kSmoothThreads), 0, s, counts, nx, ny, norm, sigma, pixel, rx, wx, tmp, zero, n_zero, done);
+    static_assert(kRowSpan == 256 && kSmoothThreads == 256, "smooth_row_blocks");
+    const unsigned blocks = (unsigned)raysh::smooth_row_blocks(wx, ny);
+    hipLaunchKernelGGL(smooth_rows_slide_kernel, dim3(blocks), dim3(kSmoothThreads), 0, s, counts, nx, ny, norm,
+                       sigma, pixel, rx, wx, tmp, zero, n_zero, done);
 }
 
 inline int taps_radius(double sigma, double pixel) { return (int)std::ceil(3.0 * sigma / pixel); }

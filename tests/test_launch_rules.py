@@ -30,6 +30,10 @@ int main() {
             RAYSH_FP64_WAVES(RAYSH_CASE)
 #undef RAYSH_CASE
             std::printf("%d %lld\n", form, threads);
+        } else if (!std::strcmp(what, "rows")) {   // threads of the row pass and of the disk's prefix sums, if they fit
+            if (std::scanf("%lld %lld", &nx, &ny) != 2) return 1;
+            const long long a = smooth_row_blocks((int)nx, (int)ny), b = disk_prefix_blocks((int)ny);
+            std::printf("%lld %lld\n", grid_fits(a, 256) ? a * 256 : 0, grid_fits(b, 256) ? b * 256 : 0);
         } else {
             return 2;
         }
@@ -77,3 +81,15 @@ def test_waves_forms_of_small_lattices(rules):
                  ("waves", 8192, 8192, 1000), ("waves", 8192, 8192, 16384)])
     assert [int(f) for f, _ in got][0] == 0 and all(f > 0 for f, _ in got[1:3])
     assert [int(f) for f, _ in got][3:] == [-1, -1]
+
+
+def test_row_passes_fit_their_grid(rules):
+    """The passes that take a wave per row serve maps of up to nearly 2^26
+    rows; taller ones, which are accepted too, are left to a thread per output."""
+    ext = _extents()
+    got = rules([("rows", wx, ny) for wx, ny in ext])
+    assert len(got) == len(ext)
+    for (wx, ny), (rows, prefix) in zip(ext, got):
+        assert rows < 2 ** 32 and prefix < 2 ** 32
+        assert rows > 0 or ny * -(-wx // 256) > 2 ** 26 - 4
+        assert prefix > 0 or ny > 2 ** 26 - 8
