@@ -2,6 +2,7 @@
 // they can be checked over extents that no test could run.
 #pragma once
 
+#include <cmath>
 #include <cstdint>
 
 namespace raysh {
@@ -74,6 +75,33 @@ inline int waves_form(int64_t nx, int64_t ny, int64_t n_stars, const TileShape &
     RAYSH_FP64_WAVES(RAYSH_CASE)
 #undef RAYSH_CASE
     return form;
+}
+
+// Ray tiles of a lattice block in the expansion mode (shoot_expansion.hip):
+// 4096 rays, w x h = 64 / 2^skew x 64 * 2^skew.
+struct TileGrid {
+    int skew, w, h;
+    int64_t tiles_x, tiles_y;
+};
+constexpr int kTileRays = 4096, kMaxSkew = 2;   // |skew|
+
+// The skew nearest to half the logarithm of dx / dy, so that the sides differ
+// by a factor of sqrt(2) at most (|skew| <= kMaxSkew): near lists, and with them
+// the stars summed directly, grow as the square of the tile's radius.  But no
+// side of twice the lattice's length or more: on a lattice of a few rows a
+// taller tile holds fewer rays, and there are more tiles (2^20 x 1 rays, 3000
+// stars, dx = 16 dy: 592 us in tiles of 64 x 64, 2245 in 16 x 256).
+inline TileGrid expansion_tiles(int64_t nx, int64_t ny, double dx, double dy) {
+    TileGrid g;
+    const double k = std::round(0.5 * std::log2(dx / dy));
+    g.skew = k >= kMaxSkew ? kMaxSkew : k <= -kMaxSkew ? -kMaxSkew : (int)k;   // (dx / dy may be 0 or infinite)
+    while (g.skew > 0 && ny <= 32 << g.skew) --g.skew;
+    while (g.skew < 0 && nx <= 32 << -g.skew) ++g.skew;
+    g.w = g.skew >= 0 ? 64 >> g.skew : 64 << -g.skew;
+    g.h = kTileRays / g.w;
+    g.tiles_x = (nx + g.w - 1) / g.w;
+    g.tiles_y = (ny + g.h - 1) / g.h;
+    return g;
 }
 
 // Workgroups of smooth_rows_slide_kernel (256 outputs of 4 rows each) and of

@@ -111,14 +111,6 @@ struct StarCellStore {
 hipError_t build_star_cells(const Star *d_stars, int64_t n_stars, hipStream_t s, StarCellStore &out);
 void free_star_cells(StarCellStore &cells);
 
-// Ray tiles of a lattice block in the expansion mode (shoot_expansion.hip):
-// tiles of w x h = 64 / 2^skew x 64 * 2^skew rays.
-struct TileGrid {
-    int skew, w, h;
-    int64_t tiles_x, tiles_y;
-};
-TileGrid expansion_tiles(int64_t nx, int64_t ny, double dx, double dy);
-
 // FP64 with the far field as local expansions (shoot_expansion.hip); tiles in
 // blocks of `block` x `block` (1, 2 or 4): one workgroup per block for the
 // pass over the stars, then one for a tile or a few.  expansion_block picks

@@ -57,14 +57,13 @@ constexpr int kOrder = 24;            // Taylor terms B_0 .. B_kOrder
 constexpr int kWaves = kThreads / 64;
 constexpr int kNearPerWave = 512;     // near-star list capacity of each wave
 constexpr int kBlockNear = kWaves * kNearPerWave;   // near stars of a block whose lists hold
-// A tile is 4096 rays, 64 x 64 for a lattice of square cells.  For others it
-// is 64 / 2^k by 64 * 2^k (expansion_tiles), so that its sides come out as equal as
-// they can: near lists, and with them the stars summed directly, grow as the
-// square of its radius.  A patch is a quarter of the tile either way.
+// A tile is 4096 rays, 64 x 64 for a lattice of square cells, for others
+// 64 / 2^k by 64 * 2^k (expansion_tiles).  A patch is a quarter of the tile
+// either way.
 constexpr int kPatchRays = 256;       // 16 x 16 / 2^k by 16 * 2^k
 constexpr int kPatchSide = 4;         // patches along a tile's sides
 constexpr int kPatches = kPatchSide * kPatchSide;
-constexpr int kMaxSkew = 2;           // |k|
+static_assert(kPatches * kPatchRays == kTileRays, "a tile's patches");
 constexpr int kPatchOrder = 14;       // Taylor terms of a patch's polynomial (see expansion_tile_kernel)
 constexpr int kTileNear = 256;        // near stars a tile keeps as a list of its own
 constexpr int kCellMaxRows = kThreads;   // star-cell grid rows and columns: one thread per row
@@ -1159,19 +1158,6 @@ int expansion_block(const TileGrid &g, int64_t n_stars, int n_cu) {
         }
     }
     return best;
-}
-
-// 64 / 2^k by 64 * 2^k rays with k nearest to half the logarithm of dx / dy,
-// so that the sides differ by a factor of sqrt(2) at most (|k| <= kMaxSkew).
-TileGrid expansion_tiles(int64_t nx, int64_t ny, double dx, double dy) {
-    TileGrid g;
-    const double k = std::round(0.5 * std::log2(dx / dy));
-    g.skew = k >= kMaxSkew ? kMaxSkew : k <= -kMaxSkew ? -kMaxSkew : (int)k;   // (dx / dy may be 0 or infinite)
-    g.w = g.skew >= 0 ? 64 >> g.skew : 64 << -g.skew;
-    g.h = kPatchRays * kPatches / g.w;
-    g.tiles_x = (nx + g.w - 1) / g.w;
-    g.tiles_y = (ny + g.h - 1) / g.h;
-    return g;
 }
 
 size_t expansion_workspace_bytes(const TileGrid &g, int block) {

@@ -34,6 +34,11 @@ int main() {
             if (std::scanf("%lld %lld", &nx, &ny) != 2) return 1;
             const long long a = smooth_row_blocks((int)nx, (int)ny), b = disk_prefix_blocks((int)ny);
             std::printf("%lld %lld\n", grid_fits(a, 256) ? a * 256 : 0, grid_fits(b, 256) ? b * 256 : 0);
+        } else if (!std::strcmp(what, "tiles")) {
+            double dx;   // dy = 1
+            if (std::scanf("%lld %lld %lf", &nx, &ny, &dx) != 3) return 1;
+            const TileGrid g = expansion_tiles(nx, ny, dx, 1.0);
+            std::printf("%d %d %lld\n", g.w, g.h, (long long)(g.tiles_x * g.tiles_y));
         } else {
             return 2;
         }
@@ -93,3 +98,20 @@ def test_row_passes_fit_their_grid(rules):
         assert rows < 2 ** 32 and prefix < 2 ** 32
         assert rows > 0 or ny * -(-wx // 256) > 2 ** 26 - 4
         assert prefix > 0 or ny > 2 ** 26 - 8
+
+
+@pytest.mark.parametrize("ratio", [1e-300, 0.05, 0.25, 0.5, 1.0, 2.0, 4.0, 20.0, 1e300])
+def test_expansion_tiles_of_thin_lattices(rules, ratio):
+    """Tiles follow the cells' aspect, but never so that a lattice of a few
+    (32) rows or columns gets more of them than tiles of 64 x 64 rays would be
+    (four times as many for 2^20 x 1 rays, three times the time)."""
+    ext = _extents()
+    got = rules([("tiles", nx, ny, ratio) for nx, ny in ext])
+    assert len(got) == len(ext)
+    for (nx, ny), (w, h, tiles) in zip(ext, got):
+        square = -(-nx // 64) * -(-ny // 64)
+        assert w * h == 4096 and tiles == -(-nx // int(w)) * -(-ny // int(h))
+        assert tiles <= (square if min(nx, ny) <= 32 else 2 * square), (nx, ny, w, h)
+    big = dict(zip(ext, got))[4096, 4096][:2]
+    assert big == {0.05: (256, 16), 0.25: (128, 32), 0.5: (128, 32), 1.0: (64, 64), 2.0: (32, 128), 4.0: (32, 128),
+                   20.0: (16, 256), 1e-300: (256, 16), 1e300: (16, 256)}[ratio]
