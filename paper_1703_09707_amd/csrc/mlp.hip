@@ -451,8 +451,9 @@ __global__ __launch_bounds__(kRowThreads) void mlp_rows_kernel(RowNet net, const
 #pragma unroll
         for (int u = 0; u < kRowAhead; ++u) w[u] = row_load(c, u);
     }
-    // the zero slots, and k past a layer's width: zero once, never written
-    // with anything else (every product's width is one of the layers')
+    // the zero slots, and k past a layer's width: zero once.  What is written
+    // there later (the input's columns beyond a narrower hidden layer) meets
+    // the zeros that pad the weights' steps
     for (int e = threadIdx.x; e < 2 * act_words / 8; e += kRowThreads) ((uint4 *)lds)[e] = uint4{0, 0, 0, 0};
     for (int e = threadIdx.x; e < 2 * h + no; e += kRowThreads)
         bias[e] = e < h ? net.b1[e] : e < 2 * h ? net.b2[e - h] : net.b3[e - 2 * h];
@@ -629,6 +630,12 @@ int check_batch(const raysh_mlp *p, int32_t batch) {
     if (batch < 1 || batch > p->max_batch)
         return set_error(RAYSH_EINVAL, "batch %d outside [1, %d]", batch, p->max_batch);
     return RAYSH_OK;
+}
+
+// Whether two of a call's buffers share memory.
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return a && b && x < y + b_bytes && y < x + a_bytes;
 }
 
 RowNet row_net(const raysh_mlp *p) {
@@ -825,7 +832,14 @@ int raysh_mlp_forward(raysh_mlp *p, const float *x, int32_t batch, float *probs)
     if (int r = validate_device_ptr(x, (size_t)batch * p->n_in * 4, p->device, "x")) return r;
     if (int r = validate_device_ptr(probs, (size_t)batch * p->n_out * 4, p->device, "probs")) return r;
     if (p->by_rows) {
-        forward_rows<false>(p, x, nullptr, batch, probs);
+        // a workgroup writes its rows' outputs while others still read x
+        const size_t out_bytes = (size_t)batch * p->n_out * 4;
+        const bool aside = overlap(x, (size_t)batch * p->n_in * 4, probs, out_bytes);
+        forward_rows<false>(p, x, nullptr, batch, aside ? p->dZ3 : probs);
+        if (aside) {
+            const hipError_t e = hipMemcpyAsync(probs, p->dZ3, out_bytes, hipMemcpyDeviceToDevice, p->stream);
+            if (e != hipSuccess) return hip_error(e, "raysh_mlp_forward");
+        }
     } else {
         forward(p, x, batch);
         hipLaunchKernelGGL(softmax_xent_kernel, dim3(batch), dim3(64), 0, p->stream, p->Z3, nullptr, batch, p->n_out,
@@ -863,9 +877,24 @@ int raysh_mlp_gradient(raysh_mlp *p, const float *x, const float *target, int32_
             g.first = tiles;
             tiles += ((g.M + 15) / 16) * g.tiles_n;
         }
-        hipLaunchKernelGGL(mlp_grad_kernel, dim3(tiles + (loss ? 1 : 0)), dim3(256), 0, s, l[0], l[1], l[2], tiles, B,
-                           G, grads, p->row_loss, loss);
-        const hipError_t e = hipGetLastError();
+        // workgroups write grads and the loss while others still read x: in buffers that
+        // share memory the loss comes after the gradient, and the caller's copy last
+        const size_t x_bytes = (size_t)B * ni * 4, g_bytes = (size_t)p->n_params * 4;
+        const bool in_turn =
+            overlap(x, x_bytes, grads, g_bytes) || overlap(x, x_bytes, loss, 4) || overlap(grads, g_bytes, loss, 4);
+        const auto launch = [&](int blocks, int n_tiles, float *copy, float *mean) {
+            hipLaunchKernelGGL(mlp_grad_kernel, dim3(blocks), dim3(256), 0, s, l[0], l[1], l[2], n_tiles, B, G, copy,
+                               p->row_loss, mean);
+        };
+        hipError_t e = hipSuccess;
+        if (!in_turn) {
+            launch(tiles + (loss ? 1 : 0), tiles, grads, loss);
+        } else {
+            launch(tiles, tiles, nullptr, nullptr);
+            if (loss) launch(1, 0, nullptr, loss);   // the workgroup past the last tile takes the loss
+            if (grads) e = hipMemcpyAsync(grads, G, g_bytes, hipMemcpyDeviceToDevice, s);
+        }
+        if (e == hipSuccess) e = hipGetLastError();
         if (e != hipSuccess) return hip_error(e, "raysh_mlp_gradient");
         p->has_grad = true;
         return set_ok();
