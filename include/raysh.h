@@ -168,7 +168,9 @@ int64_t raysh_n_stars(const raysh_ctx *ctx);
  * RAYSH_FP64 shape, lattices that would leave compute units idle in the
  * context's shape run in a form in which a workgroup's 4 to 16 waves share one
  * tile and split its stars into contiguous runs, added in order after the
- * macro term.
+ * macro term; a ray's beta then differs from the set shape's by rounding (and
+ * so may that of a band of rays from the whole lattice's, or a batch's from a
+ * single launch's).
  */
 int raysh_set_tile(raysh_ctx *ctx, int precision, int cx, int cy, int share, int star_tile);
 
@@ -300,7 +302,13 @@ int raysh_shoot(raysh_ctx *ctx, const raysh_rays *rays, int precision,
  * raysh_map: Algorithm 1 for one block of rays: ADDS one to counts[js*nx + is]
  * for every ray that lands in the window (the map is accumulated, never
  * cleared, so maps of disjoint blocks of one lattice sum to the map of the
- * whole lattice).  counts: device int32 [pix->ny][pix->nx].
+ * whole lattice).  A block's rays are the lattice's bit for bit; their sums are
+ * rounded as the launch shape and a ray's place in its tile have it, so the
+ * sum of maps is exact for RAYSH_FP64 in a shape set by raysh_set_tile or the
+ * tuner, with blocks that begin at whole tiles, and otherwise holds up to the
+ * rays whose beta lies within a rounding of a pixel's edge (none in most maps:
+ * about 1e-14 of a pixel's width on either side).
+ * counts: device int32 [pix->ny][pix->nx].
  * n_binned (optional, HOST pointer): if not NULL, the call waits for the
  * stream and stores the number of rays this call binned.
  * Errors as raysh_shoot; EINVAL also when counts is NULL or not device
@@ -337,7 +345,11 @@ int raysh_map_split_noalloc(raysh_ctx *ctx, const raysh_rays *rays, const raysh_
  * Work items (set, ray tile) are ordered longest first and drained by a
  * persistent grid from a device work queue; the launch is captured once into
  * a HIP graph per (sets, shapes) and replayed when the same batch is run again.
- * Maps are accumulated, as in raysh_map.  Errors: as raysh_map for every set,
+ * Maps are accumulated, as in raysh_map, and equal raysh_map's in the same
+ * launch shape bit for bit: always in RAYSH_FP32_BULK, in RAYSH_FP64 for
+ * contexts whose shape raysh_set_tile or the tuner has set and for lattices
+ * that fill the device; for smaller ones up to rays within a rounding of a
+ * pixel's edge (see raysh_set_tile).  Errors: as raysh_map for every set,
  * EINVAL if n_sets < 1 or the contexts are on different devices.
  */
 int raysh_map_batch(raysh_ctx *const *sets, int n_sets, const raysh_rays *rays,

@@ -53,14 +53,17 @@ constexpr double kOncePerTile = 2.4e6, kOnceShared = 6.5e5;
 // One pass in the fastest form for the lattice: `t` (the shape for lattices
 // that fill the device many times over: -1) or the waves of a workgroup sharing
 // a tile (the form's place in RAYSH_FP64_WAVES), whichever keeps the busiest
-// compute unit busy least and can be launched.  Measured (us, t and the form
-// chosen): 100 stars and 1000^2 rays 64 -> 31, 1000 and 500^2 458 -> 62, 1000
-// and 250^2 457 -> 25, 3000 and 100^2 1343 -> 58, 10000 and 2048^2 8630 ->
+// compute unit busy least and can be launched.  The forms add a ray's stars in
+// runs, t in one, as the batch kernel does, so a form has to save a twentieth:
+// lattices that fill the device have the rounding of their batch and of their
+// bands (4096^2 rays and 20000 stars would save 2 %).  Measured (us, t and the
+// form chosen): 100 stars and 1000^2 rays 64 -> 31, 1000 and 500^2 458 -> 62,
+// 1000 and 250^2 457 -> 25, 3000 and 100^2 1343 -> 58, 10000 and 2048^2 8630 ->
 // 8030; 1000 and 8192^2 stay with t (12.70 ms against 12.91, its epilogue
 // being cheaper a ray).
 inline int waves_form(int64_t nx, int64_t ny, int64_t n_stars, const TileShape &t, int n_cu) {
     if (n_cu < 1) n_cu = 1;
-    double best = 0.99 * busiest_unit(nx, ny, n_stars, t, 16 * t.cx, 16 * t.cy, 4, kOncePerTile, n_cu);
+    double best = 0.95 * busiest_unit(nx, ny, n_stars, t, 16 * t.cx, 16 * t.cy, 4, kOncePerTile, n_cu);
     int form = -1, i = 0;
 #define RAYSH_CASE(CX, CY, S, NS, W)                                                                      \
     if (grid_fits(tiles_of(nx, ny, 8 * CX, 8 * CY), 64 * W)) {                                            \

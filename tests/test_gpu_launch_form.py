@@ -83,3 +83,42 @@ def test_wide_lattice_of_few_rows(torch):
     assert abs(int(n) - int(nw)) <= 10
     assert int((m - w).abs().sum()) <= 20
     assert int(n) == int(m.sum(dtype=torch.int64)) > nx // 2
+
+
+@pytest.mark.parametrize("shape", [(8, 4, 16, 1), (2, 2, 2, 2), (4, 4, 8, 4)])
+def test_set_shape_is_exact(torch, shape):
+    """In a set shape a ray's beta is the whole lattice's, bit for bit, in every
+    block that begins at a whole tile, and a batch's maps are the single
+    launches'."""
+    nx, ny = 700, 650
+    rays, lens = _rays(nx, ny), _lens(230)
+    with R.Context(lens) as ctx:
+        _set(ctx, shape)
+        whole = _shoot(ctx, rays)
+        tw, th = 16 * shape[0], 16 * shape[1]
+        for i0, j0, w, h in ((0, 0, nx, 2 * th), (0, 3 * th, nx, 101), (2 * tw, th, 300, ny - th), (tw, 0, 33, 7)):
+            part = _shoot(ctx, rays[:4] + (w, h, i0, j0))
+            for a, b in zip(whole, part):
+                np.testing.assert_array_equal(a[j0:j0 + h, i0:i0 + w], b)
+        others = [_rays(300, 200), rays, _rays(90, 1000)]
+        single = [ctx.map(r, PIX, "fp64") for r in others]
+        batch = R.map_batch([ctx] * 3, others, [PIX] * 3, "fp64")
+        assert all(torch.equal(a, b) for a, b in zip(single, batch))
+
+
+def test_full_lattice_is_exact_by_default(torch):
+    """A lattice that fills the device: the batch's map and the sum of its
+    bands' (each of them full too) are the single launch's, with no shape set."""
+    nx = 4096
+    rays, lens = _rays(nx, 2 * nx), _lens(60)
+    with R.Context(lens) as ctx:
+        whole = ctx.map(rays, PIX, "fp64")
+        assert torch.equal(R.map_batch([ctx], [rays], [PIX], "fp64")[0], whole)
+        acc = torch.zeros_like(whole)
+        for j0 in (0, nx):
+            ctx.map(rays[:5] + (nx, 0, j0), PIX, "fp64", counts=acc)
+        assert torch.equal(acc, whole)
+        beta = ctx.shoot(rays, "fp64", PIX)
+        for j0 in (0, nx):
+            part = ctx.shoot(rays[:5] + (nx, 0, j0), "fp64", PIX)
+            assert all(torch.equal(a[j0:j0 + nx], b) for a, b in zip(beta, part))

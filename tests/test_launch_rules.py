@@ -83,9 +83,16 @@ def test_waves_forms_fit_their_grid(rules, stars):
 def test_waves_forms_of_small_lattices(rules):
     """The lattices the forms were measured on keep them."""
     got = rules([("waves", 1000, 1000, 100), ("waves", 250, 250, 1000), ("waves", 100, 100, 3000),
-                 ("waves", 8192, 8192, 1000), ("waves", 8192, 8192, 16384)])
-    assert [int(f) for f, _ in got][0] == 0 and all(f > 0 for f, _ in got[1:3])
-    assert [int(f) for f, _ in got][3:] == [-1, -1]
+                 ("waves", 2048, 2048, 10000)])
+    assert [int(f) for f, _ in got][0] == 0 and all(f > 0 for f, _ in got[1:3]) and got[3][0] == 0
+
+
+@pytest.mark.parametrize("side", [4096, 6000, 8192, 16384])
+def test_full_lattices_keep_the_set_shape(rules, side):
+    """Lattices that fill the device run in the context's shape, whose order
+    of summation a batch and the lattice's bands share."""
+    stars = [1, 100, 1000, 5000, 16384, 20000, 100_000, 1 << 24]
+    assert [int(f) for f, _ in rules([("waves", side, side, n) for n in stars])] == [-1] * len(stars)
 
 
 def test_row_passes_fit_their_grid(rules):
