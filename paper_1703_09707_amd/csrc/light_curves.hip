@@ -184,9 +184,9 @@ __global__ __launch_bounds__(kLcThreads) void light_curve_kernel(
     const double *__restrict__ mu, int nx, int ny, double x0, double y0, double ipx, double ipy,
     const double *__restrict__ xa, const double *__restrict__ ya, const double *__restrict__ xb,
     const double *__restrict__ yb, const int32_t *__restrict__ order, const double *__restrict__ sorted,
-    int64_t n_tracks, int n_samples, float inv_nf, double inv_n1, double *__restrict__ out) {
+    int64_t n_tracks, int64_t first_block, int n_samples, float inv_nf, double inv_n1, double *__restrict__ out) {
 #pragma clang fp contract(off)
-    const int64_t base = (int64_t)blockIdx.x * (kSpt * kLcThreads);
+    const int64_t base = (first_block + blockIdx.x) * (kSpt * kLcThreads);
     const int64_t total = n_tracks * (int64_t)n_samples;
     const int64_t t0 = base / n_samples;
     const int r0 = (int)(base - t0 * n_samples) + (int)threadIdx.x;
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(kLcThreads, 8) void light_curve_track_kernel(
     const double *__restrict__ mu, int nx, int ny, double x0, double y0, double ipx, double ipy,
     const double *__restrict__ xa, const double *__restrict__ ya, const double *__restrict__ xb,
     const double *__restrict__ yb, const int32_t *__restrict__ order, const double *__restrict__ sorted,
-    int64_t n_tracks, int64_t n_chunks, int chunks_per_track, int n_samples, double inv_n1,
+    int64_t n_tracks, int64_t first_block, int64_t n_chunks, int chunks_per_track, int n_samples, double inv_n1,
     double *__restrict__ out) {
 #pragma clang fp contract(off)
     // Workgroups go to the 8 XCDs in turn; each XCD takes every eighth of 32
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kLcThreads, 8) void light_curve_track_kernel(
     const unsigned block = blockIdx.x < kXcds * kParts * part   // whole parts; the rest keep their place
                                ? (turn / part * kXcds + blockIdx.x % kXcds) * part + turn % part
                                : blockIdx.x;
-    const int64_t chunk = wave_uniform((int64_t)block * (kLcThreads / 64) + threadIdx.x / 64);
+    const int64_t chunk = wave_uniform((first_block + block) * (kLcThreads / 64) + threadIdx.x / 64);
     if (chunk >= n_chunks) return;   // uniform in the wave
     const int64_t tp = chunks_per_track == 1 ? chunk
                        : chunk >> 32 == 0    ? (int64_t)((uint32_t)chunk / (uint32_t)chunks_per_track)
@@ -838,28 +838,36 @@ extern "C" int raysh_light_curves(const double *mu_s, const raysh_pixels *grid, 
 
     hipStream_t s = (hipStream_t)hip_stream;
     const double inv_n1 = n_samples > 1 ? 1.0 / (double)(n_samples - 1) : 0.0;
+    // a launch holds fewer than 2^32 threads: 2^26 tracks and more take several
+    constexpr int64_t kMostBlocks = int64_t(1) << 23;
+    static_assert(kMostBlocks * kLcThreads < int64_t(1) << 32, "threads of a launch");
     if (n_samples >= kWaveChunk / kSpt) {
         // one wave per kWaveChunk samples of a track
         const int chunks_per_track = (n_samples + kWaveChunk - 1) / kWaveChunk;
         const int64_t n_chunks = n_tracks * chunks_per_track;
         const int64_t waves_per_block = kLcThreads / 64;
-        if ((n_chunks + waves_per_block - 1) / waves_per_block > std::numeric_limits<int32_t>::max())
+        const int64_t blocks = (n_chunks + waves_per_block - 1) / waves_per_block;
+        if (blocks > std::numeric_limits<int32_t>::max())
             return set_error(RAYSH_EOVERFLOW, "more than 2^31-1 workgroups of tracks");
-        const dim3 blocks((unsigned)((n_chunks + waves_per_block - 1) / waves_per_block));
         const bool small = (int64_t)grid->nx * grid->ny < (int64_t(1) << 29) && grid->nx < 1 << 24 && grid->ny < 1 << 24;
-#define RAYSH_LAUNCH(SMALL)                                                                                      \
-    hipLaunchKernelGGL(light_curve_track_kernel<SMALL>, blocks, dim3(kLcThreads), 0, s, mu_s, grid->nx,          \
-                       grid->ny, grid->x0, grid->y0, 1.0 / grid->px, 1.0 / grid->py, xa, ya, xb, yb, order,      \
-                       sorted, n_tracks, n_chunks, chunks_per_track, n_samples, inv_n1, curves)
-        if (small) RAYSH_LAUNCH(true);
-        else RAYSH_LAUNCH(false);
+        for (int64_t first = 0; first < blocks; first += kMostBlocks) {
+            const dim3 part((unsigned)std::min(blocks - first, kMostBlocks));
+#define RAYSH_LAUNCH(SMALL)                                                                                    \
+    hipLaunchKernelGGL(light_curve_track_kernel<SMALL>, part, dim3(kLcThreads), 0, s, mu_s, grid->nx,          \
+                       grid->ny, grid->x0, grid->y0, 1.0 / grid->px, 1.0 / grid->py, xa, ya, xb, yb, order,    \
+                       sorted, n_tracks, first, n_chunks, chunks_per_track, n_samples, inv_n1, curves)
+            if (small) RAYSH_LAUNCH(true);
+            else RAYSH_LAUNCH(false);
 #undef RAYSH_LAUNCH
+        }
     } else {
         const float inv_nf = 1.0f / (float)n_samples;                   // n_samples <= 2^24: exact in float
-        hipLaunchKernelGGL(light_curve_kernel,
-                           dim3((unsigned)((total + kSpt * kLcThreads - 1) / (kSpt * kLcThreads))), dim3(kLcThreads),
-                           0, s, mu_s, grid->nx, grid->ny, grid->x0, grid->y0, 1.0 / grid->px, 1.0 / grid->py, xa, ya,
-                           xb, yb, order, sorted, n_tracks, n_samples, inv_nf, inv_n1, curves);
+        const int64_t blocks = (total + kSpt * kLcThreads - 1) / (kSpt * kLcThreads);
+        for (int64_t first = 0; first < blocks; first += kMostBlocks)
+            hipLaunchKernelGGL(light_curve_kernel, dim3((unsigned)std::min(blocks - first, kMostBlocks)),
+                               dim3(kLcThreads), 0, s, mu_s, grid->nx, grid->ny, grid->x0, grid->y0,
+                               1.0 / grid->px, 1.0 / grid->py, xa, ya, xb, yb, order, sorted, n_tracks, first,
+                               n_samples, inv_nf, inv_n1, curves);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "raysh_light_curves");
