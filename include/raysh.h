@@ -293,6 +293,8 @@ int raysh_autotune_batch(raysh_ctx *const *sets, int n_sets, const raysh_rays *r
  * EINVAL on bad rays/pixels/precision, on a NULL ctx, or when an output
  * pointer is not device memory large enough for nx*ny elements;
  * EOVERFLOW when nx*ny > 2^31 - 1 or i0 + nx, j0 + ny > 2^53.
+ * EDEVICE also when a launch would need 2^32 threads (a block of a few rows
+ * and, by the launch shape, 2^28 columns or more).
  * An empty block (nx or ny == 0) is a no-op.
  */
 int raysh_shoot(raysh_ctx *ctx, const raysh_rays *rays, int precision,

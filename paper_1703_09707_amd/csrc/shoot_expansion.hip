@@ -1071,6 +1071,9 @@ template <int L>
 hipError_t launch_level(const ShootParams &p, const StarCells &cells, double theta_open, const TileGrid &g,
                         BlockFar *far, hipStream_t s) {
     const int64_t bx = (g.tiles_x + L - 1) / L, by = (g.tiles_y + L - 1) / L;
+    const int64_t groups = L > 1 ? bx * by * (L * L / kTilesPerGroup) : 0;
+    const bool grouped = groups >= 4 * kComputeUnits;
+    if (!grid_fits(grouped ? groups : bx * by * L * L, kThreads)) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)(bx * by));
     if (cells.ncx > 0)
         hipLaunchKernelGGL(expansion_block_kernel<true>, grid, dim3(kThreads), 0, s, p, cells, theta_open, (int)bx,
@@ -1080,8 +1083,7 @@ hipError_t launch_level(const ShootParams &p, const StarCells &cells, double the
                            g.w * L, g.h * L, far);
     const bool map = p.counts && p.fast_pixels && !p.beta_x && !p.beta_y && !p.bin;
     if constexpr (L > 1) {
-        const int64_t groups = bx * by * (L * L / kTilesPerGroup);
-        if (groups >= 4 * kComputeUnits) {
+        if (grouped) {
             if (map)
                 hipLaunchKernelGGL((expansion_tile_kernel<L, kTilesPerGroup, true>), dim3((unsigned)groups),
                                    dim3(kThreads), 0, s, p, theta_open, (int)bx, g.skew, far);

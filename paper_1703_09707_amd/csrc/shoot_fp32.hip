@@ -178,6 +178,7 @@ hipError_t launch(const ShootParams &p, hipStream_t s) {
     ShootParams q = p;
     q.tiles_x = (int32_t)((p.nx + kLanesX * CX - 1) / (kLanesX * CX));
     const int64_t blocks = (int64_t)q.tiles_x * tiles_y;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;   // HIP would not say so
     hipLaunchKernelGGL((shoot_fp32_kernel<CX, CY, S>), dim3((unsigned)blocks), dim3(kThreads), 0,
                        s, q);
     return hipGetLastError();

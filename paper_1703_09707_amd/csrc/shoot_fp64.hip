@@ -676,6 +676,7 @@ hipError_t launch(const ShootParams &p, hipStream_t s) {
     ShootParams q = p;
     q.tiles_x = (int32_t)((p.nx + kLanesX * CX - 1) / (kLanesX * CX));
     const int64_t blocks = (int64_t)q.tiles_x * tiles_y;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;   // HIP would not say so
     hipLaunchKernelGGL((shoot_fp64_kernel<CX, CY, SHARE, NS>), dim3((unsigned)blocks), dim3(kThreads),
                        0, s, q);
     return hipGetLastError();
@@ -698,6 +699,7 @@ hipError_t launch_split(const ShootParams &p, int parts, double2 *partial, hipSt
     const int64_t n_tiles = (int64_t)q.tiles_x * tiles_y;
     int chunk = (int)((p.n_stars + parts - 1) / parts);
     chunk = (chunk + NS - 1) / NS * NS;
+    if (!grid_fits(n_tiles * parts, kThreads)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((partial_fp64_kernel<CX, CY, SHARE, NS>), dim3((unsigned)(n_tiles * parts)), dim3(kThreads),
                        0, s, q, n_tiles, chunk, partial);
     hipError_t e = hipGetLastError();

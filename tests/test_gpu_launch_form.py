@@ -122,3 +122,17 @@ def test_full_lattice_is_exact_by_default(torch):
         for j0 in (0, nx):
             part = ctx.shoot(rays[:5] + (nx, 0, j0), "fp64", PIX)
             assert all(torch.equal(a[j0:j0 + nx], b) for a, b in zip(beta, part))
+
+
+@pytest.mark.parametrize("precision,shape,nx", [("fp64", (2, 2, 2, 2), (1 << 29) + 3200),
+                                                ("fp32_bulk", (4, 4, 0, 128), (1 << 30) + 6400)])
+def test_grid_beyond_a_launch_is_refused(torch, precision, shape, nx):
+    """Tiles of 256 threads for a row of nx rays: 2^32 threads and some, which HIP
+    launches without an error and leaves undone."""
+    rays = (-1.25, -0.3, 2.5 / nx, 0.3, nx, 1, 0, 0)
+    with R.Context(_lens(2)) as ctx:
+        ctx.set_tile(precision, shape[0], shape[1], share=shape[2], star_tile=shape[3])
+        counts = torch.zeros((PIX[5], PIX[4]), dtype=torch.int32, device="cuda")
+        with pytest.raises(R.RayshError):
+            ctx.map(rays, PIX, precision, counts=counts)
+        assert int(counts.sum()) == 0
