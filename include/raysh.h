@@ -186,8 +186,11 @@ int raysh_set_expansion(raysh_ctx *ctx, double theta_open);
  * one tile, one test).  0 (the default) picks the block by a cost model:
  * a workgroup costs about n_stars + 16384 block^2 star-equivalents, and
  * workgroups run in rounds of three per compute unit, a part-filled round
- * counted in proportion.  The block
- * changes the order of floating-point operations, not the accuracy bound.
+ * counted in proportion.  The model does not look at the field's density: a
+ * block whose near stars exceed its lists (four of 512) has its rays sum every
+ * star directly, so a dense field over a whole lattice may need block 1 set by
+ * hand.  The block changes the order of floating-point operations, not the
+ * accuracy bound.
  * EINVAL for a NULL context or a block other than 0, 1, 2 or 4. */
 int raysh_set_expansion_block(raysh_ctx *ctx, int block);
 

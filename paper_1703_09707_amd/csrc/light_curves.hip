@@ -849,7 +849,8 @@ extern "C" int raysh_light_curves(const double *mu_s, const raysh_pixels *grid, 
         const int64_t blocks = (n_chunks + waves_per_block - 1) / waves_per_block;
         if (blocks > std::numeric_limits<int32_t>::max())
             return set_error(RAYSH_EOVERFLOW, "more than 2^31-1 workgroups of tracks");
-        const bool small = (int64_t)grid->nx * grid->ny < (int64_t(1) << 29) && grid->nx < 1 << 24 && grid->ny < 1 << 24;
+        const bool small =
+            (int64_t)grid->nx * grid->ny < (int64_t(1) << 29) && grid->nx < 1 << 24 && grid->ny < 1 << 24;
         for (int64_t first = 0; first < blocks; first += kMostBlocks) {
             const dim3 part((unsigned)std::min(blocks - first, kMostBlocks));
 #define RAYSH_LAUNCH(SMALL)                                                                                    \

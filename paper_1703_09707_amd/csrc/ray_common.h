@@ -98,9 +98,10 @@ __device__ __forceinline__ void bin_shared_init(BinShared &sh) {
 // Epilogue of a ray tile: per-ray outputs, then the counts.  Each lane holds
 // CX x CY rays: column a at block index i = tile_i + lx + 16 a, row b at
 // j = tile_j + ly + 16 b.  Counts go first into an LDS window of kWinX x kWinY
-// pixels placed around the tile's mean pixel, with a global atomic for rays outside it; the window is then merged into the map
-// with one global atomic per non-empty pixel.  Must be reached by
-// every thread of the workgroup (it contains barriers).
+// pixels placed around the tile's mean pixel, with a global atomic for rays
+// outside it; the window is then merged into the map with one global atomic
+// per non-empty pixel.  Must be reached by every thread of the workgroup (it
+// contains barriers).
 template <int CX, int CY>
 __device__ __forceinline__ void finish_tile(const ShootParams &p, BinShared &sh,
                                             const double (&tx)[CX], const double (&ty)[CY],

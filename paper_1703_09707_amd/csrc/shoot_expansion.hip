@@ -706,7 +706,7 @@ __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, con
 //      the next tile fills the other.
 // Bound by VALU issue: about 180 instructions a ray (56 Horner, 10.5 per near
 // star, 36 pixel and count, 15 for the first two phases), where 16 rays a lane
-// at order 24 took 273: 16384 stars and 8192^2 rays 650 -> 420 us; the share
+// at order 24 took 273: 16384 stars and 8192^2 rays 650 -> 430 us; the share
 // of the chip's FP64 issue rate is alike.
 // Three workgroups a compute unit: at four the registers spill.
 // MAP: counts only, with pixel_coordinate's form of the division (the usual
@@ -1136,16 +1136,21 @@ __global__ __launch_bounds__(kThreads) void star_cell_multipole_kernel(const Sta
 
 int expansion_order() { return kOrder; }
 
-// The block that minimises a simple cost model fitted on MI355X: a block
-// costs about N* + 16384 L^2 star-equivalents (its pass over all stars,
-// then L^2 tiles of Horner steps, near stars and binning), and blocks run in
-// rounds of three per compute unit, a part-filled round counted in
-// proportion.  The tiles of a block run as L workgroups, but the model
-// keeps their sum: it also keeps large blocks away from lattices of few
+// The block that minimises a simple cost model: a block costs about
+// N* + 16384 L^2 star-equivalents (its pass over all stars, then L^2 tiles of
+// Horner steps, near stars and binning), and blocks run in rounds of three
+// per compute unit, a part-filled round counted in proportion.  Keeping the
+// tiles' sum with the block also keeps large blocks away from lattices of few
 // blocks, where dense star fields would overflow a large block's near-star
-// lists (then its tiles sum every star directly).  Counting the tile
-// workgroups as separate work picked 4 x 4 blocks for the 4096^2-ray maps
-// of 512 to 50 000 stars, five times slower than 2 x 2.
+// lists (then its tiles sum every star directly).  The 16384 is of a tile
+// kernel about 1.5 times slower than the present one, star cells are taken for
+// N* stars, and the field's density is not looked at.  Measured, the choice
+// against blocks 1, 2 and 4 (us): 16384 stars, 8192^2 rays 515 of 1922, 773,
+// 482 (it is 4); 16384 and 4096^2 271 (2) of 537, 270, 200; 5000 and 2000^2 117
+// (1) of 116, 100, 112; 262144 and 4096^2 272 (2) of 554, 249, 172.  Where the
+// lists of the block it picks overflow it loses far more: 200000 stars and
+// 6000^2 rays over the whole field take 2.5 s in blocks of 4 x 4 tiles and
+// 2.8 ms in single ones (raysh_set_expansion_block).
 int expansion_block(const TileGrid &g, int64_t n_stars, int n_cu) {
     const int64_t slots = 3 * (int64_t)(n_cu > 0 ? n_cu : 256);
     int best = 1;

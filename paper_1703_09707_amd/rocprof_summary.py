@@ -29,6 +29,13 @@ KERNEL_SOURCES = {
     "expansion_block_kernel": ["csrc/shoot_expansion.hip", "csrc/ray_common.h", "csrc/raysh_internal.h"],
     "light_curve_kernel": ["csrc/light_curves.hip", "csrc/smooth.h"],
     "light_curve_track_kernel": ["csrc/light_curves.hip", "csrc/smooth.h"],
+    "waves_fp64_kernel": ["csrc/shoot_fp64.hip", "csrc/ray_common.h", "csrc/raysh_internal.h", "csrc/launch_rules.h"],
+    "mlp_rows_kernel": ["csrc/mlp.hip"],
+    "mlp_grad_kernel": ["csrc/mlp.hip"],
+    "smooth_rows_slide_kernel": ["csrc/smooth.h"],
+    "slide_cols_hist_kernel": ["csrc/histogram.hip", "csrc/smooth.h"],
+    "disk_prefix_kernel": ["csrc/light_curves.hip"],
+    "disk_map_kernel": ["csrc/light_curves.hip"],
 }
 
 
