@@ -704,7 +704,7 @@ __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, con
 //      word (a tile has 4096 rays); two windows take turns, so that a tile
 //      needs one barrier, after which its window is merged into the map while
 //      the next tile fills the other.
-// Bound by VALU issue: about 180 instructions a ray (56 Horner, 10.5 per near
+// Bound by VALU issue: about 169 instructions a ray (56 Horner, 10.5 per near
 // star, 36 pixel and count, 15 for the first two phases), where 16 rays a lane
 // at order 24 took 273: 16384 stars and 8192^2 rays 650 -> 430 us; the share
 // of the chip's FP64 issue rate is alike.
