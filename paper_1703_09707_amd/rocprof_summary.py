@@ -8,8 +8,8 @@
         --copy-mib 1024 --command "..." --out profiles/<kernel>_<workload>.txt
 
 HBM byte counters are scaled by what the same counter reads for a plain copy
-of a known size (bench.py --copy-calibration MIB copies MIB MiB three times):
-scale = expected KiB / measured KiB.  The summary records a SHA-256 of the
+of a known size (bench.py --copy-calibration MIB copies MIB MiB three times,
+the largest copies of the run): scale = expected KiB / measured KiB.  The summary records a SHA-256 of the
 kernel's sources so that a later change of the kernel invalidates it.
 """
 import argparse
@@ -70,6 +70,16 @@ def counter_values(db, name_like, grid=None):
         if grid is None or g == grid:
             out.setdefault(counter, []).append(value)
     return out
+
+
+CALIBRATION_COPIES = 3
+
+
+def calibration_copy(values):
+    """Mean counter of the calibration's copies: the largest ones, as the run
+    also copies stars, maps and results."""
+    top = sorted(values)[-CALIBRATION_COPIES:]
+    return sum(top) / len(top)
 
 
 def dispatch_durations_us(db, name_like, grid=None):
@@ -213,7 +223,7 @@ def main(argv=None):
         kern = counter_values(db, a.kernel, a.grid).get(counter)
         if not copy or not kern:
             continue
-        c = sum(copy) / len(copy)
+        c = calibration_copy(copy)
         k = sum(kern) / len(kern)
         scale = expected_kib / c
         lines.append(f"{label}_copy_kib_per_dispatch: {c:.1f}  (copy of {a.copy_mib} MiB: expected {expected_kib:.0f})")
