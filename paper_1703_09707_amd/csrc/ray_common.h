@@ -180,6 +180,66 @@ __device__ __forceinline__ void finish_tile(const ShootParams &p, BinShared &sh,
     if (threadIdx.x == 0 && p.n_binned) atomicAdd(p.n_binned, (unsigned long long)total);
 }
 
+// 1 / r[i] for N values from one hardware reciprocal (good to about 2^-24)
+// of their product, refined by one Newton step (to about 2^-48).  The
+// product is built as a balanced tree (N - 1 multiplies); walking the tree
+// back down, each node's inverse times its sibling's product is the inverse
+// of the node's other child (2 multiplies per node), so the leaves receive
+// 1 / r[i].  Cost: 3 (N - 1) multiplies, one reciprocal, two FMAs.
+template <int N>
+__device__ __forceinline__ double tree_product(const double *r) {
+    if constexpr (N == 1) return r[0];
+    else return tree_product<N / 2>(r) * tree_product<N / 2>(r + N / 2);
+}
+
+template <int N>
+__device__ __forceinline__ void tree_inverse(const double *r, double y, double *inv) {
+    if constexpr (N == 1) {
+        inv[0] = y;
+    } else {
+        const double lo = tree_product<N / 2>(r);       // common subexpressions of the up-sweep
+        const double hi = tree_product<N / 2>(r + N / 2);
+        tree_inverse<N / 2>(r, hi * y, inv);           // 1 / (product of the lower half)
+        tree_inverse<N / 2>(r + N / 2, lo * y, inv + N / 2);
+    }
+}
+
+template <int N>
+__device__ __forceinline__ void reciprocals(const double *r, double *inv) {
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8 || N == 16, "N is a power of two");
+    const double pr = tree_product<N>(r);
+    double y = __builtin_amdgcn_rcp(pr);
+    const double e = __builtin_fma(-pr, y, 1.0);
+    y = __builtin_fma(y, e, y);
+    tree_inverse<N>(r, y, inv);
+}
+
+// m / r[i] for N values that share the numerator m: the root's inverse is
+// scaled by m inside its Newton step (t = m y, then t + t e with
+// e = 1 - p y), so the leaves receive m / r[i] for one multiply per group.
+template <int N>
+__device__ __forceinline__ void scaled_reciprocals(const double *r, double m, double *inv) {
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8 || N == 16, "N is a power of two");
+    const double pr = tree_product<N>(r);
+    const double y = __builtin_amdgcn_rcp(pr);
+    const double e = __builtin_fma(-pr, y, 1.0);
+    const double t = m * y;
+    tree_inverse<N>(r, __builtin_fma(t, e, t), inv);
+}
+
+// The same with the root's inverse refined to the last place: with
+// e = 1 - p y of about 2^-25, t + t (e + e^2) leaves e^3 where t + t e leaves
+// e^2 (some 8 units of 2^-53, more than the tree's roundings), for one FMA a
+// group.
+template <int N>
+__device__ __forceinline__ void fine_scaled_reciprocals(const double *r, double m, double *inv) {
+    const double pr = tree_product<N>(r);
+    const double y = __builtin_amdgcn_rcp(pr);
+    const double e = __builtin_fma(-pr, y, 1.0);
+    const double t = m * y;
+    tree_inverse<N>(r, __builtin_fma(t, __builtin_fma(e, e, e), t), inv);
+}
+
 // Star records read through the constant address space: no kernel writes
 // them, and uniform loads from it become scalar loads whatever the kernel
 // stores elsewhere.

@@ -586,15 +586,13 @@ __device__ __forceinline__ double image_angle_at(double origin, double base, int
 constexpr int kCols = 2;
 constexpr int kRows = kPatchRays / 64;
 
-// Star (sx, sy, sm) added to a lane's rays.  Each ray's reciprocal is its own
-// (the hardware's and one Newton step).  One for all eight from a product
-// tree takes 2 instructions a ray and star less, but its six roundings more
-// made the largest error of fields with few near stars up to four times as
-// large (11861 stars, 1498 x 4096 rays, 3000 of them against 80-bit sums:
-// 1.1e-14 for 3.1e-15; RMS 6.5e-16 for 5.9e-16), and a ray's value depend on
-// the rays beside it.  With the tree and without: 16384 stars, 8192^2 rays
-// 463 and 478 us; 5000 stars, 2000^2 rays 111 and 122; 60000 stars, 3000^2
-// rays, about 300 near stars a tile, 729 and 867.
+// Star (sx, sy, sm) added to a lane's rays, one reciprocal for all eight: a
+// product tree with the mass at its root, whose inverse is refined twice.  Of a
+// star's term on its own rays the error is at most 11 units of 2^-53 (6 seen,
+// RMS 1.6); one refinement leaves up to 19 (RMS 2.4), as does a reciprocal for
+// each ray with one (RMS 2.1), which takes 16 % longer where a tile has about
+// 300 near stars (60000 stars, 3000^2 rays: 870 us for 743).  A ray on the star
+// turns all eight NaN (see expansion_tile_kernel).
 __device__ __forceinline__ void near_star(double sx, double sy, double sm, const double (&tx)[kCols],
                                           const double (&ty)[kRows], double (&ax)[kCols][kRows],
                                           double (&ay)[kCols][kRows]) {
@@ -604,19 +602,21 @@ __device__ __forceinline__ void near_star(double sx, double sy, double sm, const
         ey[k] = ty[k] - sy;
         ey2[k] = ey[k] * ey[k];
     }
+    double ex[kCols], r2[kCols * kRows], w[kCols * kRows];
 #pragma unroll
     for (int c = 0; c < kCols; ++c) {
-        const double ex = tx[c] - sx;
+        ex[c] = tx[c] - sx;
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) r2[c * kRows + k] = __builtin_fma(ex[c], ex[c], ey2[k]);
+    }
+    fine_scaled_reciprocals<kCols * kRows>(r2, sm, w);
+#pragma unroll
+    for (int c = 0; c < kCols; ++c)
 #pragma unroll
         for (int k = 0; k < kRows; ++k) {
-            const double r2 = __builtin_fma(ex, ex, ey2[k]);
-            double y = __builtin_amdgcn_rcp(r2);
-            y = __builtin_fma(y, __builtin_fma(-r2, y, 1.0), y);
-            const double w = sm * y;
-            ax[c][k] = __builtin_fma(w, ex, ax[c][k]);
-            ay[c][k] = __builtin_fma(w, ey[k], ay[c][k]);
+            ax[c][k] = __builtin_fma(w[c * kRows + k], ex[c], ax[c][k]);
+            ay[c][k] = __builtin_fma(w[c * kRows + k], ey[k], ay[c][k]);
         }
-    }
 }
 
 // Entry e of a block's near lists, one after the other; before[w] is the first
@@ -628,17 +628,29 @@ __device__ __forceinline__ int block_near(const BlockFar *f, const int (&before)
 
 // The stars a tile sums directly, one after the other, uniform in the wave:
 // all stars when the block's lists have overflowed, else the tile's near
-// stars; body(x, y, m).  They come 64 at a time, indices in the lanes, and the
-// next star's record is loaded while the current one is summed.  A tile's own
-// list gives the indices without a trip to memory; one with more near stars
-// than that takes the block's lists, of which near_of marks its own (40000
-// stars, 2000^2 rays, blocks of 2 x 2 tiles of 257 near stars and more: 523 us
-// a map, 1350 when such a tile summed all of its block's).
+// stars; body(x, y, m).  The next star's record is loaded while the current one
+// is summed (all of 16602 stars, 74 x 370 rays: 6.15 ms for 6.88 without).
+// Near stars come 64 at a time, indices in the lanes.  A tile's own list gives
+// the indices without a trip to memory; one with more near stars than that
+// takes the block's lists, of which near_of marks its own (40000 stars, 2000^2
+// rays, blocks of 2 x 2 tiles of 257 near stars and more: 431 us a map, 1027
+// when such a tile summed all of its block's).
 template <class Body>
 __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, const ConstStar *st, const BlockFar *f,
                                                 bool all, int n_stars, Body body) {
     if (all) {
-        for (int k = 0; k < n_stars; ++k) body(st[k].x, st[k].y, st[k].m);
+        if (n_stars == 0) return;
+        double sx = st[0].x, sy = st[0].y, sm = st[0].m;
+        for (int k = 1; k <= n_stars; ++k) {
+            asm volatile("" : "+s"(sx), "+s"(sy), "+s"(sm));   // as below
+            const int next = k < n_stars ? k : 0;
+            const double nx = st[next].x, ny = st[next].y, nm = st[next].m;
+            __builtin_amdgcn_sched_barrier(0);
+            body(sx, sy, sm);
+            sx = nx;
+            sy = ny;
+            sm = nm;
+        }
         return;
     }
     const int lane = threadIdx.x % 64, cnt = uniform(sh.near_n[t]);
@@ -695,7 +707,7 @@ __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, con
 //      (0.239 / (1 / theta - 0.77))^15 / (1 - 0.08) of its term: 1.1e-17
 //      for theta = 0.25 and 3.8e-16 for 0.3, at or under the rounding of the
 //      term.  One order less dropped 1.4e-16 and 4e-15: ten times the rounding
-//      at 0.3 (the order takes 8 us of the 486 of 16384 stars, 8192^2 rays).
+//      at 0.3 (the order takes 11 us of the 474 of 16384 stars, 8192^2 rays).
 //      14 instead of 24 multiply-adds a ray.
 //   3. Tile by tile, each wave evaluates four patches, four rays a lane: the
 //      polynomial by Horner, the near stars directly, the pixel, the count.
@@ -704,7 +716,7 @@ __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, con
 //      word (a tile has 4096 rays); two windows take turns, so that a tile
 //      needs one barrier, after which its window is merged into the map while
 //      the next tile fills the other.
-// Bound by VALU issue: about 169 instructions a ray (56 Horner, 10.5 per near
+// Bound by VALU issue: about 169 instructions a ray (56 Horner, 8.6 per near
 // star, 36 pixel and count, 15 for the first two phases), where 16 rays a lane
 // at order 24 took 273: 16384 stars and 8192^2 rays 650 -> 430 us; the share
 // of the chip's FP64 issue rate is alike.

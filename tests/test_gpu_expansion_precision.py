@@ -1,5 +1,5 @@
-"""The expansion mode's own error: near stars take each ray's reciprocal by
-itself, and a patch's polynomial keeps what its tile's holds."""
+"""The expansion mode's own error: a near star's term is good to the last
+places, and a patch's polynomial keeps what its tile's holds."""
 import numpy as np
 import pytest
 
@@ -19,25 +19,27 @@ def torch():
 
 
 @pytest.mark.parametrize("block", [1, 2])
-@pytest.mark.parametrize("n_stars", [1, 5, 300])
-def test_near_stars_do_not_depend_on_the_rays_beside(torch, block, n_stars):
-    """Where every star is near, a ray's beta is the same bit for bit wherever
-    in its tile it lies: each of its terms is its own, in index order.  (A
-    reciprocal shared with other rays would carry their rounding.)"""
-    rng = np.random.default_rng(n_stars)
-    d = 0.01
-    lens = (0.1, 0.15, -0.05, rng.uniform(-0.3, 0.3, n_stars), rng.uniform(-0.3, 0.3, n_stars),
-            rng.uniform(1e-3, 2e-3, n_stars))
-    with R.Context(lens) as ctx:
+@pytest.mark.parametrize("seed", range(6))
+def test_near_star_terms(torch, block, seed):
+    """One star among the rays, its term far larger than theta, against 80-bit
+    arithmetic.  Tolerance, in units of 2^-53 of each component of the term:
+    two roundings of r^2, two a level of the eight rays' product tree, one each
+    of the mass, of the root's last refinement and of the product with the
+    offset (11; the refinements leave 2^-72), and one of beta itself."""
+    L = np.longdouble
+    rng = np.random.default_rng(seed)
+    d = rng.uniform(0.01, 0.02)
+    nx, ny, m = 48, 40, 2.0 ** 30
+    rays = (-24 * d + d * rng.uniform(-0.3, 0.3), -20 * d, d, d * rng.uniform(0.9, 1.1), nx, ny, 0, 0)
+    with R.Context((0.0, 0.0, 0.0, [0.0], [0.0], [m])) as ctx:
         ctx.set_expansion_block(block)
-        at = {}
-        for i0, j0 in ((0, 0), (7, 3), (1, 22), (30, 5)):
-            rays = (-0.32, -0.32, d, d, 64 - i0, 64 - j0, i0, j0)
-            at[i0, j0] = [t.cpu().numpy() for t in ctx.shoot(rays, "fp64_expansion", PIX)]
-        whole = at[0, 0]
-        for (i0, j0), part in at.items():
-            for w, p in zip(whole, part):
-                np.testing.assert_array_equal(w[j0:, i0:], p, err_msg=f"block {block} from ray ({i0}, {j0})")
+        gx, gy, _ = (t.cpu().numpy() for t in ctx.shoot(rays, "fp64_expansion", PIX))
+    tx = (rays[0] + (np.arange(nx) + 0.5) * rays[2]).astype(L)[None, :]
+    ty = (rays[1] + (np.arange(ny) + 0.5) * rays[3]).astype(L)[:, None]
+    w = L(m) / (tx * tx + ty * ty)
+    for got, t in ((gx, tx), (gy, ty)):
+        want, term = t - w * t, np.abs(w * t)
+        assert np.all(np.abs(got - want) <= 2.0 ** -53 * (11 * term + np.abs(want)))
 
 
 @pytest.mark.parametrize("block", [1, 4])
