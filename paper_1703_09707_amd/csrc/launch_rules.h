@@ -2,6 +2,7 @@
 // they can be checked over extents that no test could run.
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -113,5 +114,20 @@ inline TileGrid expansion_tiles(int64_t nx, int64_t ny, double dx, double dy) {
 // exceeds the grid, where a thread per output does not.
 inline int64_t smooth_row_blocks(int wx, int ny) { return ((wx + (int64_t)255) / 256) * ((ny + (int64_t)3) / 4); }
 inline int64_t disk_prefix_blocks(int ny) { return 1 + (ny + (int64_t)3) / 4; }
+
+// Whether prefix sums pay for a disk's map.  Its about 0.79 (2 rx + 1)(2 ry + 1)
+// counts a pixel are read in 0.9 us each on a 2048^2 map and, as one thread's
+// chain of loads, in no less than 0.08 us on a small one; 2 (2 ry + 1) prefix
+// sums take 1.6 us each (0.05), and their making 15 us and 4 besides.
+// Directly and with them: radius 3 and 4 on 2048^2 60 us and 62, 80 and 59;
+// radius 4 and 5.5 on 1024^2 20.5 and 24.5, 32 and 26; radius 8.5 on 256^2 21.5
+// and 16.5; radius 25 on 2048^2 1770 and 200; a disk one pixel wide and any
+// height never.
+inline bool disk_by_prefix(int rx, int ry, int64_t pixels) {
+    const double maps = (double)pixels / (2048.0 * 2048.0), rows = 2.0 * ry + 1.0, cols = 2.0 * rx + 1.0;
+    const double direct = 0.79 * cols * rows * std::max(0.9 * maps, 0.08);
+    const double prefix = 2.0 * rows * std::max(1.6 * maps, 0.05) + 15.0 * maps + 4.0;
+    return prefix < direct;
+}
 
 }  // namespace raysh

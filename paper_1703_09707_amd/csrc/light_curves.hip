@@ -136,15 +136,6 @@ __global__ __launch_bounds__(kLcThreads) void disk_map_direct_kernel(const int32
     out[idx] = (norm * (double)s) / (double)(*n_taps);
 }
 
-// Whether the prefix sums pay: about 0.79 (2 rx + 1)(2 ry + 1) counts a pixel
-// are read in 0.9 us each on a 2048^2 map, against 2 (2 ry + 1) prefix sums
-// in 1.6 us each and 15 us for making them (radius 3: 49 us against 60;
-// radius 4: 67 both; radius 25: 1770 against 200; a disk one pixel wide and
-// any height never).
-inline bool disk_by_prefix(int rx, int ry) {
-    return (int64_t)(2 * ry + 1) * (4 * (2 * (int64_t)rx + 1) - 18) > 82;
-}
-
 // The same from two prefix sums per row of the disk.
 __global__ __launch_bounds__(kLcThreads) void disk_map_kernel(const long long *__restrict__ prefix, int nx,
                                                               double norm, int rx, int ry,
@@ -715,7 +706,8 @@ extern "C" int raysh_source_map(const int32_t *counts, int32_t nx, int32_t ny, d
         int *half = (int *)(n_taps + 1);                    // 2 ry + 1 < ny
         long long *prefix = n_taps + 1 + (2 * ry + 2) / 2;  // nx * ny: within the workspace, as 2 ry + 2 <= ny
         const int64_t prefix_blocks = raysh::disk_prefix_blocks(ny);
-        const bool by_prefix = disk_by_prefix(rx, ry) && raysh::grid_fits(prefix_blocks, kLcThreads);
+        const bool by_prefix =
+            raysh::disk_by_prefix(rx, ry, (int64_t)nx * ny) && raysh::grid_fits(prefix_blocks, kLcThreads);
         hipLaunchKernelGGL(disk_prefix_kernel, dim3(by_prefix ? (unsigned)prefix_blocks : 1u), dim3(kLcThreads), 0, s,
                            counts, nx, ny, size, px, py, rx, ry, half, n_taps, prefix);
         if (by_prefix)

@@ -34,6 +34,9 @@ int main() {
             if (std::scanf("%lld %lld", &nx, &ny) != 2) return 1;
             const long long a = smooth_row_blocks((int)nx, (int)ny), b = disk_prefix_blocks((int)ny);
             std::printf("%lld %lld\n", grid_fits(a, 256) ? a * 256 : 0, grid_fits(b, 256) ? b * 256 : 0);
+        } else if (!std::strcmp(what, "disk")) {
+            if (std::scanf("%lld %lld %lld", &nx, &ny, &n) != 3) return 1;
+            std::printf("%d\n", (int)disk_by_prefix((int)nx, (int)ny, n));
         } else if (!std::strcmp(what, "tiles")) {
             double dx;   // dy = 1
             if (std::scanf("%lld %lld %lf", &nx, &ny, &dx) != 3) return 1;
@@ -122,3 +125,13 @@ def test_expansion_tiles_of_thin_lattices(rules, ratio):
     big = dict(zip(ext, got))[4096, 4096][:2]
     assert big == {0.05: (256, 16), 0.25: (128, 32), 0.5: (128, 32), 1.0: (64, 64), 2.0: (32, 128), 4.0: (32, 128),
                    20.0: (16, 256), 1e-300: (256, 16), 1e300: (16, 256)}[ratio]
+
+
+def test_disk_rule(rules):
+    """Prefix sums where they were measured to be faster, counts where those
+    were: radii in pixels, map sides."""
+    direct = [(1, 1, 2048), (3, 3, 2048), (4, 4, 1024), (4, 4, 724), (4, 4, 501), (0, 1000, 4096)]
+    prefix = [(4, 4, 2048), (5, 5, 1024), (6, 6, 724), (6, 6, 501), (8, 8, 512), (8, 8, 128), (12, 12, 256),
+              (25, 25, 2048), (2, 80, 8192)]
+    got = rules([("disk", rx, ry, n * n) for rx, ry, n in direct + prefix])
+    assert [int(g[0]) for g in got] == [0] * len(direct) + [1] * len(prefix)
