@@ -591,7 +591,7 @@ constexpr int kRows = kPatchRays / 64;
 // star's term on its own rays the error is at most 11 units of 2^-53 (6 seen,
 // RMS 1.6); one refinement leaves up to 19 (RMS 2.4), as does a reciprocal for
 // each ray with one (RMS 2.1), which takes 16 % longer where a tile has about
-// 300 near stars (60000 stars, 3000^2 rays: 870 us for 743).  A ray on the star
+// 300 near stars (60000 stars, 3000^2 rays: 873 us for 736).  A ray on the star
 // turns all eight NaN (see expansion_tile_kernel).
 __device__ __forceinline__ void near_star(double sx, double sy, double sm, const double (&tx)[kCols],
                                           const double (&ty)[kRows], double (&ax)[kCols][kRows],
@@ -716,9 +716,9 @@ __device__ __forceinline__ void for_tile_direct(const TileShared &sh, int t, con
 //      word (a tile has 4096 rays); two windows take turns, so that a tile
 //      needs one barrier, after which its window is merged into the map while
 //      the next tile fills the other.
-// Bound by VALU issue: about 169 instructions a ray (56 Horner, 8.6 per near
+// Bound by VALU issue: about 167 instructions a ray (56 Horner, 8.6 per near
 // star, 36 pixel and count, 15 for the first two phases), where 16 rays a lane
-// at order 24 took 273: 16384 stars and 8192^2 rays 650 -> 430 us; the share
+// at order 24 took 273: 16384 stars and 8192^2 rays 650 -> 425 us; the share
 // of the chip's FP64 issue rate is alike.
 // Three workgroups a compute unit: at four the registers spill.
 // MAP: counts only, with pixel_coordinate's form of the division (the usual
@@ -1157,12 +1157,12 @@ int expansion_order() { return kOrder; }
 // lists (then its tiles sum every star directly).  The 16384 is of a tile
 // kernel about 1.5 times slower than the present one, star cells are taken for
 // N* stars, and the field's density is not looked at.  Measured, the choice
-// against blocks 1, 2 and 4 (us): 16384 stars, 8192^2 rays 515 of 1922, 773,
-// 482 (it is 4); 16384 and 4096^2 271 (2) of 537, 270, 200; 5000 and 2000^2 117
-// (1) of 116, 100, 112; 262144 and 4096^2 272 (2) of 554, 249, 172.  Where the
-// lists of the block it picks overflow it loses far more: 200000 stars and
-// 6000^2 rays over the whole field take 2.5 s in blocks of 4 x 4 tiles and
-// 2.8 ms in single ones (raysh_set_expansion_block).
+// against blocks 1, 2 and 4 (us): 16384 stars, 8192^2 rays 4 of 1930, 765, 474;
+// 16384 and 4096^2 2 of 523, 250, 186; 5000 and 2000^2 1 of 102, 89, 101;
+// 262144 and 4096^2 2 of 559, 245, 168.  Where the lists of the block it picks
+// overflow it loses far more: 200000 stars and 6000^2 rays over the whole field
+// take 1.8 s in blocks of 4 x 4 tiles and 2.4 ms in single ones
+// (raysh_set_expansion_block).
 int expansion_block(const TileGrid &g, int64_t n_stars, int n_cu) {
     const int64_t slots = 3 * (int64_t)(n_cu > 0 ? n_cu : 256);
     int best = 1;
